@@ -129,3 +129,28 @@ def test_quantize_weights_rule_near_thresholds(Q, fmt):
             r[pos] = rng.choice([-1.0, 1.0], pos.size) * 40.0 * 2.0 ** -rng.integers(47, 59, pos.size)
             rows.append(r)
     check(Q, np.array(rows, dtype=np.float32), 64, fmt)
+
+
+@pytest.mark.parametrize("K,b", [(64, 64), (4096, 4096), (4160, 64), (16384, 4096)])
+def test_scale_search_full_bins_and_ties(Q, K, b):
+    # Rows that rotate exactly (one or two nonzeros per block, sqrt(b) a power of two): equal magnitudes
+    # throughout (every element in one histogram bin: the largest count and sum), candidates whose errors
+    # tie (all-equal rows), blocks far below the maximum (no element past the first threshold) and
+    # magnitudes on the thresholds of single candidates; PoT and G(r), bit for bit.
+    def row(*vals):
+        r = np.zeros(K)
+        for i in range(K // b):
+            a, d = vals[i % len(vals)]
+            r[i * b + 3], r[i * b + 9] = a, d
+        return r
+
+    rows = [row((16, 0)), row((-16, 0), (16, 0)), row((48, 16)), row((24, 8), (8, 0)), row((1024, 0), (1, 0)),
+            row((1024, 0), (640, 0)), row((256, 0), (32, 0)), row((16, 16)), row((3, 1), (2, 1), (5, 2)), row((0, 0))]
+    W = np.array(rows, dtype=np.float32)
+    check(Q, W, b, levels.FMT_W2_POT, exact=True)
+    w = hadamard.rotate_weights(W.astype(np.float64), b)
+    for r in (0.25, 0.3, 0.9):
+        C, s = Q.quantize_weights_mirror(torch.from_numpy(W).cuda(), b, r)
+        C_ref, s_ref = quant.quantize_mirror_mse(w, r)
+        assert np.array_equal(s.cpu().numpy().view(np.uint16), s_ref.view(np.uint16)), f"scales r={r}"
+        assert np.array_equal(C.cpu().numpy(), C_ref), f"codes r={r}"

@@ -306,7 +306,7 @@ class SweepStack:
         self.acts = [qift.alloc_act(self.M, K, dev) for (_, _, K, _, _) in self.plan]
         self.outs = [torch.empty((self.M, N), dtype=torch.float16, device=dev) for (_, N, _, _, _) in self.plan]
         # one workspace for the linears that take one at this M (the skinny linear split over K up to 64
-        # tokens, the FP4 x FP6 GEMM above)
+        # tokens, the GEMM split over K above)
         self.need = [qift.workspace_bytes(w, self.M) for w in self.weights[0]]
         self.ws = torch.empty(max(self.need), dtype=torch.uint8, device=dev) if max(self.need) else None
         torch.cuda.synchronize()
@@ -929,17 +929,10 @@ def main():
                 w = pre.weights[layer][i]
                 qift.rotate_quant_act(pre.x[i], blk, out=pre.acts[i])
                 ops = 2 * pre.M * N * K
-                # the int8 MFMA kernel; for MNZ also the FP4 x FP6 scaled-MFMA kernel (its workspace
-                # selects it; the FP6 re-coding of the activations is inside the timed call)
-                variants = [("int8 MFMA", None)]
-                if qift.workspace_bytes(w, pre.M):
-                    variants.append(("FP4 x FP6 MFMA", torch.empty(qift.workspace_bytes(w, pre.M),
-                                                                   dtype=torch.uint8, device="cuda")))
-                for path, ws in variants:
-                    dt = _time_graph(torch, lambda: qift.linear(w, pre.acts[i], out=pre.outs[i], workspace=ws, use_sum=True), 10)
-                    per_shape.append({"linear": name, "format": fname, "path": path, "N": N, "K": K,
-                                      "us": round(dt * 1e6, 2), "int8_tops": round(ops / dt / 1e12, 2),
-                                      "pct_int8_peak": round(100 * ops / dt / 1e12 / INT8_PEAK_TOPS, 2)})
+                dt = _time_graph(torch, lambda: qift.linear(w, pre.acts[i], out=pre.outs[i], use_sum=True), 10)
+                per_shape.append({"linear": name, "format": fname, "path": "int8 MFMA", "N": N, "K": K,
+                                  "us": round(dt * 1e6, 2), "int8_tops": round(ops / dt / 1e12, 2),
+                                  "pct_int8_peak": round(100 * ops / dt / 1e12 / INT8_PEAK_TOPS, 2)})
         out["prefill"] = {"workload": "LLaMA-3.1-8B-shaped prefill, M=2048, layers 0-15 W4 / 16-31 W2 MNZ, "
                                       "4 rotate_quant_act + 4 linears per layer (q|k|v and gate|up stacked "
                                       "along N), one hipGraph",

@@ -308,21 +308,14 @@ int qift_w2a4_linear(const qift_packed_w *w, const int8_t *act_q, const float *a
  *              output: it is taken as is).  NULL: summed in the kernel.
  *   acc_out    out, nullable: int32 [M][N], the exact accumulators.
  *   workspace, workspace_bytes   optional device scratch (16-byte aligned).
- *              NULL / 0 runs the int8 MFMA kernels.  With at least
+ *              NULL / 0: no linear is split over K.  With at least
  *              qift_workspace_bytes(w, M) bytes, where that is not 0 (MNZ
  *              and PoT weights):
- *                M > 64 (and from M = 33 on N >= 16384, or N >= 4096 with
- *                K > 4096), where the prefill
- *                GEMM's 256-row x 64-token tiles are few (about 65-1024
- *                tokens, by N): the int8 GEMM split
- *                over K, int32 partial sums of each K-range in the
- *                workspace, then added and the epilogue applied;
- *                M > 64 otherwise: the activations are re-coded to FP6 E2M3
- *                in it and the prefill contraction runs on the FP4 x FP6
- *                scaled MFMA: the MNZ code c read as FP4 E2M1 is c / 2, the
- *                PoT levels +-1, +-4 are E2M1 values, and every partial sum
- *                stays exact in fp32 (split over K too where its tiles are
- *                few);
+ *                M > 64 (and from M = 33 on N >= 4096 with K > 4096), where
+ *                the GEMM's 256-row x 64-token tiles are few for the length of
+ *                K: the int8 GEMM split over K, int32 partial sums of each
+ *                K-range in the workspace, then added and the epilogue
+ *                applied; else the unsplit GEMM;
  *                M <= 64 otherwise (K > 4096, few 16-row tiles; up to 16 tokens only
  *                where the codes exceed the decode kernel's LDS): the decode
  *                linear is split over K, int32 partial sums of each K-range in
@@ -358,7 +351,7 @@ int qift_w2a4_lut_linear(const qift_packed_w *w, const uint16_t *lut, const int8
 
 /* The W4 sibling (fmt QIFT_W4_SYM); same arguments and results.  The workspace of the _ex call is
  * used where qift_workspace_bytes is not 0: the int8 prefill GEMM split over K, as for W2 but from 24
- * tokens on for the wide and long linears (no FP4 form). */
+ * tokens on for the wide and long linears. */
 int qift_w4a4_linear(const qift_packed_w *w, const int8_t *act_q, const float *act_scale,
                      int64_t M, uint16_t *out, qift_stream_t stream);
 int qift_w4a4_linear_ex(const qift_packed_w *w, const int8_t *act_q, const float *act_scale,
@@ -575,10 +568,9 @@ int qift_kv4_attention_decode_noalloc(const uint16_t *q, int64_t B, int32_t Hq, 
  *     over S = min(ceil(512 / T), floor(512 / T), floor(steps / s0)) K-ranges when that is at least S0
  *     (W2: 256-k steps, s0 = 4, S0 = 2; W4: 128-k steps, s0 = 8, S0 = 3): S * M * N4 int32 partial
  *     sums (256-byte aligned), then S * M int32 code sums.
- *   M > 64 otherwise, MNZ and PoT: the FP4 x FP6 prefill kernel's M * 3K/4 bytes of FP6 codes and
- *     M * ceil(K / 8192) int32 code sums, split over S = min(ceil(512 / T), floor(768 / T),
- *     floor(ceil(K / 256) / 4)) K-ranges when that is at least 2, the S * M * N4 int32 partial sums
- *     following at the next multiple of 256 bytes; W4: 0.
+ *   M > 64 otherwise, MNZ and PoT: M * 3K/4 bytes and M * ceil(K / 8192) words and, for
+ *     S = min(ceil(512 / T), floor(768 / T), floor(ceil(K / 256) / 4)) when that is at least 2, S * M * N4
+ *     words at the next multiple of 256 bytes (accepted, and not used by the present kernels); W4: 0.
  *   M <= 64 otherwise, MNZ and PoT: the decode linear split over K, where it applies (K > 4096 and at most 680
  *     16-row tiles, N <= 10880; up to 16 tokens only where the codes exceed the decode kernel's LDS):
  *     S * M * N4 int32 partial sums (256-byte aligned) and S * M int32 code sums; W4: 0. */

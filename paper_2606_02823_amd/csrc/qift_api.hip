@@ -115,8 +115,7 @@ int linear_common(const qift_packed_w* w, bool w4, const int8_t* act_q, const fl
                   size_t ws_bytes, qift_stream_t stream) {
   int st = check_linear(w, w4, act_q, act_scale, act_sum, M, out, acc_out);
   if (st != QIFT_OK) return st;
-  // the workspace is optional: none selects the int8 kernels, one of at least qift_workspace_bytes
-  // the FP4 x FP6 prefill kernel where that query is not 0
+  // the workspace is optional: one of at least qift_workspace_bytes lets the linears split over K
   const size_t need = qift_workspace_bytes(w, M);
   if (ws_bytes > 0 && (!ws || ws_bytes < need)) return QIFT_ERR_WORKSPACE;
   if (ws && !aligned16(ws)) return QIFT_ERR_ALIGN;
@@ -576,8 +575,7 @@ size_t qift_workspace_bytes(const qift_packed_w* w, int64_t M) {
   if (split != 0 || w->fmt == QIFT_W4_SYM) return split;
   if (M <= qift::kSkinnyMaxM)   // the skinny linear split over K
     return qift::skinny_workspace(w->fmt, w->N, w->K, M);
-  // the FP4 x FP6 kernel
-  return qift::gemm_f4_workspace(w->N, M, w->K);
+  return qift::gemm_w2_workspace(w->N, M, w->K);
 }
 
 const char* qift_status_string(int status) {

@@ -1,0 +1,405 @@
+// Tiled GEMM on v_mfma_i32_32x32x32_i8 for prompts (M > 64 tokens), W2 and W4 weights.
+#include "qift_fwht.h"   // buffer-load helpers
+#include "qift_internal.h"
+#include "qift_mma.h"
+
+#include <type_traits>
+
+namespace qift {
+namespace {
+
+using namespace mma;
+
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ v16i mfma32_i8(v4i a, v4i b, v16i c) {
+  return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+}
+
+constexpr int kBK = 128;                       // k per step
+template <int FMT>
+constexpr int wload16() { return FMT == FMT_W4 ? 2 : 1; }   // 16-byte loads per row tile, half wave and step
+template <int FMT>
+constexpr int line_steps() { return FMT == FMT_W4 ? 2 : 4; }   // steps in 128 bytes of a weight row
+
+// register r of the MFMA operand s of a lane's weights of one step (decode_unit, one register)
+template <int FMT>
+__device__ __forceinline__ int decode_part(const uint4 (&u)[FMT == FMT_W4 ? 2 : 1], int s, int r) {
+  if constexpr (FMT == FMT_W4) {
+    const uint4 h = u[s >> 1];
+    const uint32_t w = (s & 1) ? (r < 2 ? h.z : h.w) : (r < 2 ? h.x : h.y);
+    return (int)((r & 1 ? w >> 4 : w) & 0x0F0F0F0Fu);
+  } else {
+    const uint32_t w = s == 0 ? u[0].x : s == 1 ? u[0].y : s == 2 ? u[0].z : u[0].w;
+    const uint32_t c = (w >> (2 * r)) & 0x03030303u;
+    return FMT == FMT_POT ? (int)__builtin_amdgcn_perm(0u, 0x0401FFFCu, c) : (int)c;   // {-4, -1, +1, +4}
+  }
+}
+
+// slot of 16-byte column c of activation row r
+__device__ __forceinline__ int slot(int r, int c) { return c ^ (((r >> 1) & 7) ^ ((r & 1) << 2)); }
+
+// Tiles of 256 weight rows x 32 TC tokens, steps of 128 k.  Four waves, two workgroups to a CU; wave w owns
+// weight rows [64 w, +64) (two 32-row MFMA tiles) and all the tokens: 2 TC accumulator tiles, whose 32-wide
+// MFMA holds the int8 rate better than the 16-wide one (33 cycles per 65536 operations against 39).
+//
+// What bounds it: the chip's power.  The MFMAs alone, on registers of such codes, reach 3.2-3.5 POP/s here
+// (the clock falls to about 1.8 GHz); with one LDS read to two MFMAs and the weights' decode 3.2.  So the
+// design spends little on anything else: the packed weights go from memory straight to registers, decoded
+// once per 32 TC tokens; the int8 activations go to LDS without passing registers; consecutive MFMAs share
+// an operand; no instruction waits inside a step.
+//   weights      a lane loads its rows' 128-byte lines (512 k of W2, 256 k of W4) one line ahead, in two
+//                register sets; half wave h holds k = 128 q + 64 h .. + 63 of step q of the line.
+//   activations  four LDS buffers, filled three steps ahead by direct-to-LDS loads.  The buffers are distinct
+//                arrays, so the compiler sees that loads into one never alias reads from another and adds
+//                no waits of its own.  Rows are 128 bytes; 16-byte column c of row r lies in slot(r, c),
+//                which spreads 8 and 16 consecutive rows over the banks (5 % of LDS cycles conflict).
+//   tiles        in the order of the XCDs: a workgroup's neighbours in its L2 share tokens and weights.
+//   outputs      through LDS (the idle activation buffers), then whole rows of 512 bytes.
+// At 2048 tokens, us before (256 x 64 tiles of 16-wide MFMAs, three workgroups to a CU) -> now: W2 28672 x
+// 4096 221 -> 187 (2.57 POP/s), 4096 x 4096 40 -> 33, 4096 x 14336 105 -> 94; W4 253 -> 206, 49 -> 36, 137 ->
+// 108.  At 512: W2 73 -> 56, 27.2 -> 17.3, 66.7 -> 51.
+// With SUMQ (no per-token sums given) wave t also adds up the codes of token tile t.
+template <int FMT, int TC, bool SUMQ>
+__global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ P, const uint16_t* __restrict__ sw,
+                                                     int N, int K, const int8_t* __restrict__ act,
+                                                     const float* __restrict__ sx, const int32_t* __restrict__ asum,
+                                                     int M, int tiles_n, int tiles_m, uint16_t* __restrict__ y,
+                                                     int32_t* __restrict__ acc_out) {
+  constexpr int BM = 32 * TC;
+  constexpr int NB = wload16<FMT>(), LS = line_steps<FMT>();
+  constexpr int NA = BM * kBK / 4096;   // direct-to-LDS loads per wave and step
+  constexpr int NW = 2 * NB * LS;       // weight loads per wave and line group
+  __shared__ __align__(16) int8_t lds0[BM * kBK];
+  __shared__ __align__(16) int8_t lds1[BM * kBK];
+  __shared__ __align__(16) int8_t lds2[BM * kBK];
+  __shared__ __align__(16) int8_t lds3[BM * kBK];
+
+  __shared__ __align__(16) float s_sx[BM];
+  __shared__ __align__(16) int s_sum[BM];
+  __shared__ __align__(16) uint16_t s_sw[256];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, h = lane >> 5;
+  // tile of this workgroup: consecutive tiles of one XCD (workgroups go round the 8 XCDs) share weights
+  // and tokens in its L2
+  int tn, tm;
+  {
+    const int T = tiles_n * tiles_m;
+    const int id = blockIdx.x, x = id & 7, base = T >> 3, rem = T & 7;
+    const int tile = x * base + (x < rem ? x : rem) + (id >> 3);
+    constexpr int GT = 8;
+    const int grp = tile / (GT * tiles_n), first = grp * GT;
+    const int width = tiles_m - first < GT ? tiles_m - first : GT;
+    const int in = tile - grp * GT * tiles_n;
+    tn = in / width;
+    tm = first + in - tn * width;
+  }
+  const int n_base = tn * 256 + wave * 64;
+  const int m_base = tm * BM;
+  const int64_t rowbytes = FMT == FMT_W4 ? (int64_t)K / 2 : (int64_t)K / 4;
+  const int KT = (K + kBK - 1) / kBK;
+
+  const __amdgpu_buffer_rsrc_t wrs = dev::make_rsrc(P, (uint32_t)(N * rowbytes));
+  uint32_t wbase[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int n = n_base + 32 * j + r32;
+    wbase[j] = n < N ? (uint32_t)(n * rowbytes) + 16u * NB * h : dev::kOutOfRange;
+  }
+  auto load_w = [&](uint4 (&w)[LS][2][NB], int kt) {   // the 128 bytes from step kt on
+    const uint32_t ko = (uint32_t)kt * (32u * NB);
+#pragma unroll
+    for (int q = 0; q < LS; ++q)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w[q][j][b] = dev::bload16(wrs, wbase[j] + ko + 32u * NB * q + 16u * b);
+  };
+  const int mrows = M - m_base < BM ? M - m_base : BM;
+  const __amdgpu_buffer_rsrc_t ars = dev::make_rsrc(act + (int64_t)m_base * K, (uint32_t)(mrows * K));
+  uint32_t abase[NA];
+  int acol[NA];
+#pragma unroll
+  for (int q = 0; q < NA; ++q) {
+    const int row = 8 * (NA * wave + q) + (lane >> 3);
+    acol[q] = 16 * slot(row, lane & 7);
+    abase[q] = row < mrows ? (uint32_t)(row * K + acol[q]) : dev::kOutOfRange;
+  }
+  auto issue_a = [&](int kt, int8_t* dst, int q) {
+    const int ko = kt * kBK;
+    uint32_t off = abase[q] + (uint32_t)ko;
+    if (acol[q] + ko >= K) off = dev::kOutOfRange;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        ars, (__attribute__((address_space(3))) void*)(dst + 1024 * (NA * wave + q)), 16, off, 0, 0, 0);
+  };
+
+  v16i acc[2][TC];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int t = 0; t < TC; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[j][t][i] = 0;
+  int sq = 0;
+
+  int boff[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) boff[s] = r32 * kBK + 16 * slot(r32, 4 * h + s);
+
+  // One step of 16 pairs of MFMAs (pair i = 4 s + t: operand s of the lane's weights against token tile
+  // t, both row tiles).  Pair i reads the token operand of pair i + 3 and decodes a quarter of the
+  // weight operands of s + 1, so neither is waited for; the barrier that hands the buffers over comes
+  // after pair 12, when this wave's operand reads of the step are done, and the last pairs already
+  // read the next step's buffer.
+  v4i a[2], an[2], bq[4];
+  auto read_b = [&](const int8_t* tileb, int i) {
+    const uint4 bb = *reinterpret_cast<const uint4*>(tileb + 32 * kBK * (i % TC) + boff[i / TC]);
+    return v4i{(int)bb.x, (int)bb.y, (int)bb.z, (int)bb.w};
+  };
+  auto step = [&](const int8_t* cur, int8_t* own, const int8_t* nxt, const uint4 (&w)[2][NB],
+                  const uint4 (&wnx)[2][NB], int kt, auto outstanding) {
+    constexpr int NP = 4 * TC, OUT = decltype(outstanding)::value;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int s = i / TC, t = i % TC;
+      const v4i b = bq[i & 3];
+      // the last two pairs read three operands of the next step
+      if (i + 3 < NP) bq[(i + 3) & 3] = read_b(cur, i + 3);
+      if (i == NP - 2) {
+        bq[0] = read_b(nxt, 0);
+        bq[1] = read_b(nxt, 1);
+      }
+      if (i == NP - 1) bq[2] = read_b(nxt, 2);
+      const int j0 = t & 1;   // consecutive MFMAs share an operand
+      acc[j0][t] = mfma32_i8(a[j0], b, acc[j0][t]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 4 * t / TC; r < 4 * (t + 1) / TC; ++r)
+          an[j][r] = s < 3 ? decode_part<FMT>(w[j], s + 1, r) : decode_part<FMT>(wnx[j], 0, r);
+      if (i >= NP - 2) {
+#pragma unroll
+        for (int q = 0; q < NA / 2; ++q) issue_a(kt + 4, own, q + (i - (NP - 2)) * (NA / 2));
+      }
+      acc[1 - j0][t] = mfma32_i8(a[1 - j0], b, acc[1 - j0][t]);
+      if constexpr (SUMQ) {   // the sums of token tile t by wave t
+        // (its last read of the step before the barrier)
+        if (i == 3 * TC - 1 || (t == 0 && s < 3)) {
+          const int sr = i == 3 * TC - 1 ? 3 : s;
+          sq = sum16_i8(*reinterpret_cast<const uint4*>(cur + 32 * kBK * (wave & (TC - 1)) + boff[sr]), sq);
+        }
+      }
+      if (t == TC - 1) {
+        a[0] = an[0];
+        a[1] = an[1];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (i == NP - 3) {
+        __builtin_amdgcn_s_waitcnt(0x0070 | (OUT & 15) | ((OUT >> 4) << 14));   // vmcnt(OUT) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  auto issue_all = [&](int kt, int8_t* dst) {
+#pragma unroll
+    for (int q = 0; q < NA; ++q) issue_a(kt, dst, q);
+  };
+
+  // scales and sums of the tile for the epilogue (their loads go out before the tile's)
+  const float sx_pre = tid < mrows ? sx[m_base + tid] : 0.f;
+  int sum_pre = 0;
+  if constexpr (!SUMQ) sum_pre = tid < mrows ? asum[m_base + tid] : 0;
+  const uint16_t sw_pre = tn * 256 + tid < N ? sw[tn * 256 + tid] : (uint16_t)0;
+  __builtin_amdgcn_sched_barrier(0);
+  uint4 wa[LS][2][NB], wb[LS][2][NB];
+  load_w(wa, 0);
+  issue_all(0, lds0);
+  issue_all(1, lds1);
+  issue_all(2, lds2);
+  issue_all(3, lds3);
+  if (tid < BM) {
+    s_sx[tid] = sx_pre;
+    if constexpr (!SUMQ) s_sum[tid] = sum_pre;
+  }
+  s_sw[tid] = sw_pre;
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0070 | ((3 * NA) & 15) | (((3 * NA) >> 4) << 14));
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) bq[i] = read_b(lds0, i);
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[j][r] = decode_part<FMT>(wa[0][j], 0, r);
+  // A line group of W2 is four steps, of W4 two (whose buffers rotate over two groups).  The handover of
+  // step k waits for the activations of step k + 1, sent three steps earlier: those of steps k + 2 and
+  // k + 3 (2 NA) and the weight loads issued since (NW a group, nw of the group before) stay in flight.
+#define QIFT_GROUP4(k, w, wn, nw)                                                              \
+  step(lds0, lds0, lds1, w[0], w[1], k, std::integral_constant<int, 2 * NA + nw>());           \
+  step(lds1, lds1, lds2, w[1], w[2], k + 1, std::integral_constant<int, 2 * NA + nw>());       \
+  step(lds2, lds2, lds3, w[2], w[3], k + 2, std::integral_constant<int, 2 * NA + nw>());       \
+  step(lds3, lds3, lds0, w[3], wn[0], k + 3, std::integral_constant<int, 2 * NA>());
+#define QIFT_GROUP2(k, b0, b1, b2, w, wn, nw)                                                  \
+  step(b0, b0, b1, w[0], w[1], k, std::integral_constant<int, 2 * NA + 2 * nw>());             \
+  step(b1, b1, b2, w[1], wn[0], k + 1, std::integral_constant<int, 2 * NA + nw>());
+  auto load_w_here = [&](uint4 (&w)[LS][2][NB], int kt) {
+    load_w(w, kt);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int kt = 0;
+  for (; kt + LS < KT; kt += 2 * LS) {
+    load_w_here(wb, kt + LS);
+    if constexpr (LS == 4) {
+      QIFT_GROUP4(kt, wa, wb, NW)
+      load_w_here(wa, kt + 2 * LS);
+      QIFT_GROUP4(kt + 4, wb, wa, NW)
+    } else {
+      QIFT_GROUP2(kt, lds0, lds1, lds2, wa, wb, NW)
+      load_w_here(wa, kt + 2 * LS);
+      QIFT_GROUP2(kt + 2, lds2, lds3, lds0, wb, wa, NW)
+    }
+  }
+  // an odd last group, with no weights to load after it (a load of weights that no MFMA uses would be
+  // dropped by the compiler, and must not be counted in flight)
+  if (kt < KT) {
+    if constexpr (LS == 4) {
+      QIFT_GROUP4(kt, wa, wa, 0)
+    } else {
+      QIFT_GROUP2(kt, lds0, lds1, lds2, wa, wa, 0)
+    }
+  }
+#undef QIFT_GROUP4
+#undef QIFT_GROUP2
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // the loads past K have landed before a buffer is reused
+  __syncthreads();
+
+  if constexpr (SUMQ) {
+    sq += __shfl_xor(sq, 32);
+    if (wave < TC && h == 0) s_sum[32 * wave + r32] = sq;
+    __syncthreads();
+  }
+  float sxt[TC];
+  int sqt[TC];
+#pragma unroll
+  for (int t = 0; t < TC; ++t) {
+    sxt[t] = s_sx[32 * t + r32];
+    sqt[t] = s_sum[32 * t + r32];
+  }
+  // D of tile (j, t): register 4 q + i of lane (token r32, half h) is row 32 j + 8 q + 4 h + i
+  if (acc_out == nullptr) {
+    // through LDS: token tile t in buffer t as rows of 256 outputs (32 chunks of 8, chunk c of token m in
+    // slot c ^ m), then 16-byte stores of whole rows
+    // (with two token tiles 16 tokens to a buffer)
+    auto row_at = [&](int t, int r) -> int8_t* {
+      if constexpr (TC == 4) return (t == 0 ? lds0 : t == 1 ? lds1 : t == 2 ? lds2 : lds3) + 512 * r;
+      else if (r & 16) return (t == 0 ? lds1 : lds3) + 512 * (r & 15);
+      else return (t == 0 ? lds0 : lds2) + 512 * (r & 15);
+    };
+    static_assert(TC == 4 || TC == 2, "outputs staged in the activation buffers");
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint2 swq = *reinterpret_cast<const uint2*>(s_sw + 64 * wave + 32 * j + 8 * q + 4 * h);
+        const uint16_t s4[4] = {(uint16_t)(swq.x & 0xFFFFu), (uint16_t)(swq.x >> 16), (uint16_t)(swq.y & 0xFFFFu),
+                                (uint16_t)(swq.y >> 16)};
+#pragma unroll
+        for (int t = 0; t < TC; ++t) {
+          uint32_t o[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = epilogue(finish_acc<FMT>(acc[j][t][4 * q + i], sqt[t]), sxt[t], s4[i]);
+          const int c = 8 * wave + 4 * j + q;
+          *reinterpret_cast<uint2*>(row_at(t, r32) + 16 * (c ^ r32) + 8 * h) =
+              make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+        }
+      }
+    __syncthreads();
+    const int nt = N - tn * 256 < 256 ? N - tn * 256 : 256;   // rows of the tile below N
+    if ((N & 7) == 0) {
+      const int c = tid & 31;
+      if (8 * c < nt) {
+#pragma unroll
+        for (int t = 0; t < TC; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int r = 8 * i + (tid >> 5), m = m_base + 32 * t + r;
+            const uint4 d = *reinterpret_cast<const uint4*>(row_at(t, r) + 16 * (c ^ r));
+            if (m < M) *reinterpret_cast<uint4*>(y + (int64_t)m * N + tn * 256 + 8 * c) = d;
+          }
+      }
+    } else if (tid < nt) {   // rows of y at any alignment: one output a thread, a token at a time
+#pragma unroll
+      for (int t = 0; t < TC; ++t)
+        for (int r = 0; r < 32; ++r) {
+          const int m = m_base + 32 * t + r;
+          if (m < M)
+            y[(int64_t)m * N + tn * 256 + tid] =
+                *reinterpret_cast<const uint16_t*>(row_at(t, r) + 16 * ((tid >> 3) ^ r) + 2 * (tid & 7));
+        }
+    }
+    return;
+  }
+#pragma unroll
+  for (int t = 0; t < TC; ++t) {
+    const int m = m_base + 32 * t + r32;
+    if (m < M) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          store4_sw<FMT>(v4i{acc[j][t][4 * q], acc[j][t][4 * q + 1], acc[j][t][4 * q + 2], acc[j][t][4 * q + 3]}, m,
+                         n_base + 32 * j + 8 * q + 4 * h, N, sxt[t], sqt[t],
+                         *reinterpret_cast<const uint2*>(s_sw + 64 * wave + 32 * j + 8 * q + 4 * h), y, acc_out);
+    }
+  }
+}
+
+template <int FMT, int TC>
+hipError_t launch_t(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act, const float* sx,
+                    const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s) {
+  const int tn = (int)((N + 255) / 256), tm = (int)((M + 32 * TC - 1) / (32 * TC));
+  const dim3 grid((unsigned)tn * (unsigned)tm);
+  if (asum)
+    hipLaunchKernelGGL((k_gemm32<FMT, TC, false>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum,
+                       (int)M, tn, tm, y, acc_out);
+  else
+    hipLaunchKernelGGL((k_gemm32<FMT, TC, true>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum,
+                       (int)M, tn, tm, y, acc_out);
+  return hipGetLastError();
+}
+
+// 128 or 64 tokens to a tile.  A CU runs one or two workgroups (512 at once on the chip); relative times
+// of a tile alone on its CU and of two there, measured at K = 4096 (us of 27 / 45 and 17 / 30 for W2, 28 /
+// 54 and 22 / 40 for W4): whole rounds of two and then the rest decide.  128-token tiles halve the weight
+// loads and decodes per MFMA, 64-token tiles fill the chip from half as many tokens on (4096 x 4096 at 400
+// tokens 16.7 us against 25.1; 28672 x 4096 at 2048 tokens 213 against 187).
+inline int64_t tile_cost(int64_t tiles, int one, int two) {
+  const int64_t rest = tiles % 512;
+  return tiles / 512 * two + (rest == 0 ? 0 : rest <= 256 ? one : two);
+}
+
+template <int FMT>
+hipError_t launch_f(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act, const float* sx,
+                    const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s) {
+  const int64_t tn = (N + 255) / 256, t128 = tn * ((M + 127) / 128), t64 = tn * ((M + 63) / 64);
+  const bool wide = FMT == FMT_W4 ? tile_cost(t128, 28, 54) <= tile_cost(t64, 22, 40)
+                                  : tile_cost(t128, 27, 45) <= tile_cost(t64, 17, 30);
+  return wide ? launch_t<FMT, 4>(P, sw, N, K, act, sx, asum, M, y, acc_out, s)
+              : launch_t<FMT, 2>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+}
+
+}  // namespace
+
+hipError_t launch_gemm32(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
+                         const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s) {
+  switch (fmt) {
+    case FMT_MNZ: return launch_f<FMT_MNZ>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    case FMT_POT: return launch_f<FMT_POT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    case FMT_W4: return launch_f<FMT_W4>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace qift

@@ -47,22 +47,19 @@ hipError_t launch_rotate_quant_act(const uint16_t* x, int64_t M, int64_t K, int 
                                    int clip_den, int8_t* act_q, float* act_scale, int32_t* act_sum,
                                    hipStream_t s, bool bf16 = false);   // x fp16, or bf16 bits
 
-// Quantized linear (qift_linear.hip).  fmt selects the decode.  ws (nullable): at M > 64 the GEMM split
-// over K where gemm_split_workspace(fmt, N, M, K) (its bytes) is not 0, else for MNZ and PoT weights the
-// FP4 x FP6 MFMA kernel with gemm_f4_workspace(N, M, K) bytes.
+// Quantized linear (qift_linear.hip).  fmt selects the decode.  ws (nullable) serves the linears split over
+// K: gemm_split_workspace(fmt, N, M, K) bytes where that is not 0, else up to 64 tokens
+// skinny_workspace(fmt, N, K, M), else for MNZ and PoT weights a workspace of gemm_w2_workspace(N, M, K)
+// bytes is asked for (the sizes that callers have allocated so far) and not used.
 size_t gemm_split_workspace(int fmt, int64_t N, int64_t M, int64_t K);
+size_t gemm_w2_workspace(int64_t N, int64_t M, int64_t K);
 hipError_t launch_linear(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,
                          const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
                          uint16_t* out, int32_t* acc_out, void* ws, hipStream_t s);
 
-// MNZ and PoT prefill on the FP4 x FP6 scaled MFMA (qift_prefill_f4.hip): act_q re-coded to FP6
-// into ws (gemm_f4_workspace(N, M, K) bytes), then the GEMM, split over K into int32 partial sums in
-// ws where its tiles are few; results identical to the int8 kernel.
-constexpr int64_t kGemmF4MinM = 65;
-size_t gemm_f4_workspace(int64_t N, int64_t M, int64_t K);
-hipError_t launch_gemm_f4(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
-                          const int8_t* act_q, const float* sx, const int32_t* asum, int64_t M, uint16_t* y,
-                          int32_t* acc_out, void* ws, hipStream_t s);
+// Tiled GEMM of prompts and of wide linears from 33 tokens on (qift_gemm.hip).
+hipError_t launch_gemm32(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
+                         const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s);
 
 // Fused rotation + quantization + linear for a few decode tokens, one launcher
 // per weight format (qift_fused_<fmt>.hip).

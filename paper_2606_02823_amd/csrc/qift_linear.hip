@@ -1,6 +1,6 @@
 // Quantized linear kernels on int8 MFMA (operand layout and decoding:
-// qift_mma.h): the decode kernels for up to 16 tokens and the tiled prefill
-// GEMM.
+// qift_mma.h): the decode kernels for up to 16 tokens, the tiled GEMM split over
+// K, and the choice of kernel for a linear on codes.
 #include "qift_fwht.h"   // buffer-load helpers
 #include "qift_internal.h"
 #include "qift_mma.h"
@@ -323,37 +323,32 @@ __device__ __forceinline__ v4i gemm_operand(const uint4& u, int s) {
 }
 
 // ===========================================================================
-// Prefill kernel: tiles of 256 weight rows x 16 TT tokens, BK-k steps (BK = 256 for W2, 128 for W4).
+// GEMM split over K: tiles of 256 weight rows x 64 tokens, BK-k steps (BK = 256 for W2, 128 for W4).
 //
 // Workgroup = 4 waves; wave w owns weight rows [64 w, +64) of the tile (4
 // MFMA row tiles) and all tokens (TT column tiles): 4 TT int32 accumulator
 // tiles.  Each wave reads its own packed weights straight into registers
 // (one 16-byte load per lane per row tile and step: S MFMAs' worth of A
-// operands) one step ahead, alternating between two register sets (the k
-// loop is unrolled by two).  W4 steps over half as many k as W2, so both
-// formats hold the same weight registers and a wave fits 3 per SIMD (OCC =
-// 3: three workgroups per CU hide each other's load latency and barriers).
-// The activation tile [16 TT][BK] int8 is double-buffered in LDS and filled
-// one step ahead by direct-to-LDS buffer loads (no staging registers).  The
+// operands).  The activation tile [16 TT][BK] int8 is filled by
+// direct-to-LDS buffer loads (no staging registers).  Weights and activations
+// arrive two steps ahead, in three register sets and three LDS buffers.  The
 // tile has no row padding: the 16-byte column c of row r sits in slot
 // c ^ (r mod SL) of the row (SL = BK / 16 slots), which spreads the rows an
-// MFMA operand read touches over the banks.  The two buffers are distinct
+// MFMA operand read touches over the banks.  The buffers are distinct
 // arrays, so the compiler can tell that the loads into one never alias the
 // operand reads from the other and waits for them only at the end of the
 // step.
 // ===========================================================================
 // With SUMQ (no per-token sums given) wave w also adds up the codes of token tiles t = w (mod 4): one
 // more 16-byte LDS read and four dot products per MFMA operand step of its own tile(s).
-// SPLIT (three stages only): workgroup z of the grid's third dimension takes the steps [z us, (z + 1) us)
-// and writes its int32 accumulators to part [z][M][N rounded up to 4] (and, with SUMQ, workgroup column
-// 0 its range's code sums to psum [z][M]) instead of the outputs.
-template <int FMT, int OCC, int TT, bool SUMQ, int NS, bool SPLIT = false>
-__global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ P, const uint16_t* __restrict__ sw,
-                                                   int N, int K, const int8_t* __restrict__ act,
-                                                   const float* __restrict__ sx, const int32_t* __restrict__ asum,
-                                                   int M, uint16_t* __restrict__ y, int32_t* __restrict__ acc_out,
-                                                   int us = 0, int32_t* __restrict__ part = nullptr,
-                                                   int32_t* __restrict__ psum = nullptr) {
+// Workgroup z of the grid's third dimension takes the steps [z us, (z + 1) us) and writes its int32
+// accumulators to part [z][M][N rounded up to 4] and, with SUMQ, workgroup column 0 its range's code sums
+// to psum [z][M].
+template <int FMT, bool SUMQ>
+__global__ __launch_bounds__(256, 2) void k_gemm_split(const uint32_t* __restrict__ P, int N, int K,
+                                                       const int8_t* __restrict__ act, int M, int us,
+                                                       int32_t* __restrict__ part, int32_t* __restrict__ psum) {
+  constexpr int TT = 4;
   constexpr int S = gemm_ops<FMT>();
   constexpr int BK = gemm_bk<FMT>();
   constexpr int SL = BK / 16;            // 16-byte slots per activation row
@@ -361,13 +356,11 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ 
   constexpr int BM = 16 * TT;            // tokens per workgroup: every wave covers all of them
   constexpr int NQ = BM * BK / 4096;     // direct-to-LDS loads per wave and step
   static_assert(NQ >= 1 && RPC * SL == 64, "tile geometry");
-  // two distinct arrays (not one indexed by the step's parity), so that the compiler can tell that
-  // the direct-to-LDS loads into one never alias the operand reads from the other
+  // distinct arrays (not one indexed by the step), so that the compiler can tell that the direct-to-LDS
+  // loads into one never alias the operand reads from another
   __shared__ __align__(16) int8_t lds0[BM * BK];
   __shared__ __align__(16) int8_t lds1[BM * BK];
-  __shared__ __align__(16) int8_t lds2[NS == 3 ? BM * BK : 16];
-  static_assert(NS == 2 || NS == 3, "pipeline depth");
-  static_assert(!SPLIT || NS == 3, "a split runs three stages");
+  __shared__ __align__(16) int8_t lds2[BM * BK];
   constexpr int NL = NQ + 4;   // vector-memory loads a wave issues per step
 
   // the wave index as a scalar, so that the LDS destinations of the direct-to-LDS loads are scalar too
@@ -377,8 +370,8 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ 
   const int m_base = blockIdx.y * BM;
   const int64_t rowbytes = FMT == FMT_W4 ? (int64_t)K / 2 : (int64_t)K / 4;
   const int KA = (K + BK - 1) / BK;
-  const int kt0 = SPLIT ? (int)blockIdx.z * us : 0;
-  const int KT = SPLIT ? (kt0 + us < KA ? kt0 + us : KA) : KA;   // steps past this workgroup's range
+  const int kt0 = (int)blockIdx.z * us;
+  const int KT = kt0 + us < KA ? kt0 + us : KA;   // steps past this workgroup's range
 
   const __amdgpu_buffer_rsrc_t wrs = dev::make_rsrc(P, (uint32_t)(N * rowbytes));
   // Load offsets are a per-lane base (the out-of-range offset for rows past N, which stays out of
@@ -433,20 +426,17 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ 
 #pragma unroll
   for (int t4 = 0; t4 < TT / 4; ++t4) sq[t4] = 0;
 
-  // one step: prefetch step kt + NS - 1 (activations into pfb, weights into wpf), MFMAs of step kt from
-  // tileb and wc; the k loop is unrolled by NS so the weight registers rotate instead of being copied.
+  // one step: prefetch step kt + 2 (activations into pfb, weights into wpf), MFMAs of step kt from
+  // tileb and wc; the k loop is unrolled by three so the weight registers rotate instead of being copied.
   // MFMA s of lane group g covers k = kt BK + 16 (S g + s) .. + 15 (slot S g + s).
-  // With three stages the prefetch is issued on every step, past K too (activation loads out of range,
+  // The prefetch is issued on every step, past K too (activation loads out of range,
   // weight loads of bytes no MFMA uses), so that every path issues the same loads and the compiler's
   // wait counts stay exact across the loop.
   auto step = [&](int kt, const int8_t* tileb, int8_t* pfb, const uint4 (&wc)[4], uint4 (&wpf)[4]) {
-    const bool more = NS == 3 || kt + 1 < KT;
-    if (more) {
-      issue_a(kt + NS - 1, pfb);   // a buffer every wave finished reading before the last barrier
-      load_w(wpf, kt + NS - 1);
-    }
+    issue_a(kt + 2, pfb);   // a buffer every wave finished reading before the last barrier
+    load_w(wpf, kt + 2);
     // the loads stay ahead of the step's MFMAs (unguarded, the scheduler sinks them to the barrier)
-    if constexpr (NS == 3) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       v4i a[4];
@@ -469,30 +459,17 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ 
         }
       }
     }
-    // this wave's loads of step kt+1 have landed (vmcnt with lgkmcnt and expcnt untouched): with three
-    // stages the NL loads of step kt+2 just issued may still be in flight
-    if constexpr (NS == 3) {
-      // a bare barrier (a workgroup fence would also wait for the loads of step kt+2 into LDS), after
-      // this wave's operand reads of step kt have returned: the buffer is refilled from the next step on
-      __builtin_amdgcn_s_waitcnt(0x0070 | NL);   // vmcnt(NL) lgkmcnt(0)
-      __builtin_amdgcn_s_barrier();
-    } else {
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      __syncthreads();
-    }
+    // this wave's loads of step kt+1 have landed (vmcnt with lgkmcnt and expcnt untouched); the NL loads of
+    // step kt+2 just issued may still be in flight.  A bare barrier (a workgroup fence would also wait for
+    // the loads of step kt+2 into LDS), after this wave's operand reads of step kt have returned: the
+    // buffer is refilled from the next step on.  (In the last steps the compiler drops the weight loads
+    // that no MFMA uses: the count then lets up to four loads of step kt+1 be in flight, and those are
+    // its weights, sent after its activations.)
+    __builtin_amdgcn_s_waitcnt(0x0070 | NL);   // vmcnt(NL) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
   };
 
-  if constexpr (NS == 2) {
-    uint4 wa[4], wb[4];
-    issue_a(0, lds0);
-    load_w(wa, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    for (int kt = 0; kt < KT; kt += 2) {
-      step(kt, lds0, lds1, wa, wb);
-      if (kt + 1 < KT) step(kt + 1, lds1, lds0, wb, wa);
-    }
-  } else {
+  {
     uint4 w0[4], w1[4], w2[4];
     issue_a(kt0, lds0);
     load_w(w0, kt0);
@@ -528,32 +505,19 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ 
     }
     __syncthreads();
   }
-  if constexpr (SPLIT) {
-    const int np = (N + 3) & ~3;
-#pragma unroll
-    for (int t = 0; t < TT; ++t) {
-      const int m = m_base + 16 * t + r16;
-      if (m < M) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n0 = n_base + 16 * j + 4 * g;
-          if (n0 < N)
-            *reinterpret_cast<int4*>(part + ((size_t)blockIdx.z * M + m) * np + n0) =
-                make_int4(acc[j][t][0], acc[j][t][1], acc[j][t][2], acc[j][t][3]);
-        }
-        if (SUMQ && blockIdx.x == 0 && wave == 0 && g == 0) psum[(size_t)blockIdx.z * M + m] = s_q[16 * t + r16];
-      }
-    }
-    return;
-  }
+  const int np = (N + 3) & ~3;
 #pragma unroll
   for (int t = 0; t < TT; ++t) {
     const int m = m_base + 16 * t + r16;
     if (m < M) {
-      const float s_x = sx[m];
-      const int sqm = SUMQ ? s_q[16 * t + r16] : asum[m];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) store4<FMT>(acc[j][t], m, n_base + 16 * j + 4 * g, N, s_x, sqm, sw, y, acc_out);
+      for (int j = 0; j < 4; ++j) {
+        const int n0 = n_base + 16 * j + 4 * g;
+        if (n0 < N)
+          *reinterpret_cast<int4*>(part + ((size_t)blockIdx.z * M + m) * np + n0) =
+              make_int4(acc[j][t][0], acc[j][t][1], acc[j][t][2], acc[j][t][3]);
+      }
+      if (SUMQ && blockIdx.x == 0 && wave == 0 && g == 0) psum[(size_t)blockIdx.z * M + m] = s_q[16 * t + r16];
     }
   }
 }
@@ -561,31 +525,13 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(const uint32_t* __restrict__ 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// GEMM pipeline depth and workgroups per CU of the 256 x 64 tiles, per weight format.  W4 steps over
-// 128 k (half the MFMAs of a W2 step), so one step ahead does not cover its loads: three stages at two
-// workgroups per CU (M = 512: down 111 -> 72 us, gate|up 104 -> 90, q|k|v 36 -> 30; M = 2048 within
-// 3 %).  W2 at three stages needs two workgroups per CU too, and loses more to that than it gains
-// (gate|up at M = 2048 254 -> 285 us).
-template <int FMT>
-constexpr int gemm_stages() { return FMT == FMT_W4 ? 3 : 2; }
-template <int FMT>
-constexpr int gemm_occ() { return FMT == FMT_W4 ? 2 : 3; }
 // Above 64 tokens with a workspace, where the 256 x 64 tiles are few (down at 65-512 tokens: 16 x
-// ceil(M / 64) tiles, each a chain of 56 W2 or 112 W4 steps whose loads are not hidden), the GEMM is
-// split over K at three stages and two workgroups per CU: S ranges of at least 4 W2 or 8 W4 steps
-// (1024 k), about 512 workgroups and no more than are resident at once.  W2 (at 65 / 128 / 1024
-// tokens): down 78.3 / 81.0 / 98.7 -> 19.6 / 23.8 / 63.1 us, q|k|v 35.1 -> 11.6 at 65, o 35.3 -> 11.1;
-// it replaces the FP4 x FP6 kernel split the same way (down 25.4 / 29.4 / 80.3 us: the FP6 re-coding
-// is a launch of its own).  W4 takes at least three ranges (two measured no faster: gate|up at 128
-// tokens 31.1 -> 33.4 us, q|k|v at 512 30.0 -> 32.4): down at 65 / 128 / 512 tokens 71.9 / 72.5 /
-// 74.8 -> 22.1 / 25.0 / 46.6 us, q|k|v and o at 65 26.6 -> 11.3 / 10.9.
-// From 33 tokens on, a wide linear (N >= 16384: gate|up) or a long one (N >= 4096, K > 4096: down)
-// takes the split GEMM instead of the skinny kernel, whose workgroups each read all M x K codes
-// (gate|up at 33 / 64 tokens, W2 22.9 / 27.6 -> 18.6 / 24.3 us, W4 35.3 / 45.2 -> 22.4 / 27.0; down,
-// W2 12.7 / 16.1 -> 11.6 / 15.3, W4 21.6 / 30.5 -> 14.8 / 17.6).  Smaller linears lose: W2 q|k|v at 33
-// tokens 8.2 -> 10.1, 1000 x 14336 at 64 11.0 -> 12.8.  W4, whose skinny kernel reads twice the weight
-// bytes, from 24 tokens on (at 32: down 18.3 -> 14.4, gate|up 25.9 -> 22.0; at 24 a 22016-row gate|up
-// loses 17.8 -> 18.6 while the others gain 1.2-2.7 us).
+// ceil(M / 64) tiles, each a chain of 56 W2 or 112 W4 steps whose loads are not hidden), the GEMM may be
+// split over K at two workgroups per CU: S ranges of at least 4 W2 or 8 W4 steps (1024 k), about 512
+// workgroups and no more than are resident at once.  At 65 / 128 / 1024 tokens, W2 (the unsplit GEMM):
+// down 20 / 24 / 62 us (49 / 49 / 75).  W4 takes at least three ranges (two measured no faster).  From 33
+// tokens on (W4 24) wide (N >= 16384) and long (N >= 4096, K > 4096) linears have a plan too.  The plan
+// sizes the workspace; take_split says where it is the faster.
 constexpr int64_t kSplitTarget = 512, kSplitResident = 512, kSplitWideMinM = 33, kSplitWideMinMW4 = 24,
                   kSplitWideMinN = 16384,
                   kSplitLongMinN = 4096, kSplitLongMinK = 4097;
@@ -599,7 +545,7 @@ inline GemmSplit gemm_split_plan(int fmt, int64_t N, int64_t M, int64_t K) {
   p.us = (int)KT;
   const bool wide = M >= (fmt == FMT_W4 ? kSplitWideMinMW4 : kSplitWideMinM) &&
                     (N >= kSplitWideMinN || (N >= kSplitLongMinN && K >= kSplitLongMinK));
-  if (M < kGemmF4MinM && !wide) return p;
+  if (M <= kSkinnyMaxM && !wide) return p;
   int64_t S = (kSplitTarget + tiles - 1) / tiles;
   if (S > kSplitResident / tiles) S = kSplitResident / tiles;
   if (S > KT / min_steps) S = KT / min_steps;
@@ -609,6 +555,28 @@ inline GemmSplit gemm_split_plan(int fmt, int64_t N, int64_t M, int64_t K) {
   return p;
 }
 
+// Whether the split plan is also the faster choice.  A short K (below 8192) has few steps to share out
+// and pays the second pass (4-5 us) and the partial sums: it splits only while the tiles are few, W2 up
+// to 64 of them (4096 x 4096, split against not, us: 12.4 / 16.5 at 100 tokens, 14.5 / 16.5 at 256, but
+// 19 / 16.6 at 300 and 27 / 17.8 at 600; 12288 x 4096 19.9 / 17.5 at 100), W4 up to 96 (6144 x 4096 21.5 /
+// 22.3 at 192, 24 / 22.3 at 300).  Wide linears of a short K do not split where the GEMM takes them
+// (gemm_wide).  A long K splits wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at
+// 1024).
+inline bool gemm_wide(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
+  // From 33 tokens on a wide linear (gate|up) takes the tiled GEMM rather than the skinny kernel, whose
+  // workgroups each read all M x K codes (28672 x 4096 at 33 / 64 tokens: W2 22.9 -> 17.3 / 28.2 -> 18.6 us,
+  // W4 36.6 -> 25.6 / 46.8 -> 27.6), and unsplit (W2 20.0 -> 17.1 / 24.7 -> 18.0 at 33 / 64 with a
+  // workspace), except a long K and, below 49 tokens, W4 with a workspace (25.0 -> 25.6, 22.8 -> 24.2 at 33).
+  if (N < kSplitWideMinN || M < kSplitWideMinM) return false;
+  return !ws || (K < 8192 && (fmt != FMT_W4 || M > 48));
+}
+inline bool take_split(const GemmSplit& p, int fmt, int64_t N, int64_t M, int64_t K) {
+  if (p.S < 2) return false;
+  if (K >= 8192 || M <= kSkinnyMaxM) return !gemm_wide(fmt, N, M, K, true);
+  const int64_t tiles = ((N + 255) / 256) * ((M + 63) / 64);
+  return tiles <= (fmt == FMT_W4 ? 96 : 64) && !gemm_wide(fmt, N, M, K, true);
+}
+
 template <int FMT, bool SUMQ>
 hipError_t launch_gemm_split(const GemmSplit& p, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
                            const int8_t* act, const float* sx, const int32_t* asum, int64_t M, uint16_t* y,
@@ -616,8 +584,8 @@ hipError_t launch_gemm_split(const GemmSplit& p, const uint32_t* P, const uint16
   int32_t* part = static_cast<int32_t*>(ws);
   int32_t* psum = reinterpret_cast<int32_t*>(static_cast<unsigned char*>(ws) + split::part_bytes(p.S, M, N));
   const dim3 grid((unsigned)((N + 255) / 256), (unsigned)((M + 63) / 64), (unsigned)p.S);
-  hipLaunchKernelGGL((k_gemm<FMT, 2, 4, SUMQ, 3, true>), grid, dim3(256), 0, s, P, sw, (int)N,
-                     (int)K, act, sx, asum, (int)M, y, acc_out, p.us, part, psum);
+  hipLaunchKernelGGL((k_gemm_split<FMT, SUMQ>), grid, dim3(256), 0, s, P, (int)N, (int)K, act, (int)M, p.us, part,
+                     psum);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // code sums of range z at psum[z M + m]
@@ -686,17 +654,14 @@ template <int FMT>
 hipError_t launch_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                       const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
                       hipStream_t s) {
-  // with a workspace the GEMM split over K where that applies (above 64 tokens, or a wide or long linear
-  // from 33 on), else above 64 tokens for W2 the FP4 x FP6 kernel
   if (ws) {
     const GemmSplit p = gemm_split_plan(FMT, N, M, K);
-    if (p.S > 1)
+    if (take_split(p, FMT, N, M, K))
       return asum ? launch_gemm_split<FMT, false>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s)
                   : launch_gemm_split<FMT, true>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
-    if constexpr (FMT != FMT_W4) {
-      if (M >= kGemmF4MinM) return launch_gemm_f4(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
-    }
   }
+  if (gemm_wide(FMT, N, M, K, ws != nullptr))
+    return launch_gemm32(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
   // 17..64 tokens: the skinny kernel, one pass over the weights (the codes of that many tokens do not
   // fit the decode kernel's LDS, and the GEMM's grid of N/256 workgroups would leave most CUs idle)
   if (M > kCodesMaxM && M <= kSkinnyMaxM && K <= kSkinnyMaxK)
@@ -720,32 +685,7 @@ hipError_t launch_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t 
     if (M * kpad_of(K) <= kDecodeMaxLds) return launch_deep<FMT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
     return launch_decode<FMT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
   }
-  const unsigned gx = (unsigned)((N + 255) / 256);
-  // 256 x 64 tiles (gemm_occ, gemm_stages).  W4 on grids that fill the chip at least twice over with
-  // 256 x 128 tiles (two per CU) takes those instead: half the weight loads and decode per MFMA
-  // (stacked gate|up at M = 2048: 318 -> 264 us).  W2 does not gain from them (222 -> 225 us), and
-  // smaller grids lose to the idle CUs (q,k,v W4 74 -> 78 us).  Also measured slower at M = 2048: 256 x 32 tiles and activations staged through
-  // registers.
-  if constexpr (FMT == FMT_W4) {
-    const unsigned gy8 = (unsigned)((M + 127) / 128);
-    if ((uint64_t)gx * gy8 >= 1024) {
-      if (asum)
-        hipLaunchKernelGGL((k_gemm<FMT, 2, 8, false, 2>), dim3(gx, gy8), dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx,
-                           asum, (int)M, y, acc_out);
-      else
-        hipLaunchKernelGGL((k_gemm<FMT, 2, 8, true, 2>), dim3(gx, gy8), dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx,
-                           asum, (int)M, y, acc_out);
-      return hipGetLastError();
-    }
-  }
-  const dim3 grid(gx, (unsigned)((M + 63) / 64));
-  if (asum)
-    hipLaunchKernelGGL((k_gemm<FMT, gemm_occ<FMT>(), 4, false, gemm_stages<FMT>()>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum, (int)M,
-                       y, acc_out);
-  else
-    hipLaunchKernelGGL((k_gemm<FMT, gemm_occ<FMT>(), 4, true, gemm_stages<FMT>()>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum, (int)M,
-                       y, acc_out);
-  return hipGetLastError();
+  return launch_gemm32(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
 }
 
 }  // namespace
@@ -753,6 +693,19 @@ hipError_t launch_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t 
 size_t gemm_split_workspace(int fmt, int64_t N, int64_t M, int64_t K) {
   const GemmSplit p = gemm_split_plan(fmt, N, M, K);
   return p.S > 1 ? split::part_bytes(p.S, M, N) + (size_t)p.S * (size_t)M * 4 : 0;
+}
+
+// M 3K/4 bytes, M ceil(K / 8192) words and, for the S K-ranges of three workgroups per CU where that is at
+// least two, the partial sums at the next multiple of 256 bytes.
+size_t gemm_w2_workspace(int64_t N, int64_t M, int64_t K) {
+  const size_t base = (size_t)M * (size_t)(3 * (K / 4)) + (size_t)M * (size_t)((K / 32 + 255) / 256) * 4;
+  const int64_t tiles = ((N + 255) / 256) * ((M + 63) / 64), KT = (K + 255) / 256;
+  int64_t S = (512 + tiles - 1) / tiles;
+  if (S > 768 / tiles) S = 768 / tiles;
+  if (S > KT / 4) S = KT / 4;
+  if (S < 2) return base;
+  const int64_t us = (KT + S - 1) / S;
+  return (base + 255) / 256 * 256 + split::part_bytes((int)((KT + us - 1) / us), M, N);
 }
 
 hipError_t launch_linear(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,

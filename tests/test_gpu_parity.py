@@ -653,3 +653,39 @@ def test_hbm_read_probe_reads_every_word(Q, nwords):
     seg = Q.READ_PROBE_SEGMENT // 4
     expect = [np.bitwise_xor.reduce(words[i:i + seg]) for i in range(0, nwords, seg)]
     assert np.array_equal(host(parts).view(np.uint32), np.array(expect, dtype=np.uint32))
+
+
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("M,N,K", [(65, 264, 64), (128, 256, 128), (97, 520, 576), (129, 1000, 1536), (200, 999, 1664),
+                                   (64, 16400, 704), (33, 16384, 1088), (130, 28672, 640), (200, 22016, 1536),
+                                   (256, 16390, 320)])
+def test_tiled_gemm(Q, fmt, M, N, K):
+    # The tiled GEMM's edges: K from half a step (128 k) over partial and odd line groups (512 k of W2,
+    # 256 k of W4: K = 1536 is three of W2's, K = 320 one and a quarter of W4's); tokens that end inside a
+    # 32-token tile; rows that end inside a 256-row tile; outputs at 16-byte, 4-byte and odd offsets (N
+    # mod 8); 64-token tiles (few tiles) and 128-token tiles (the last three shapes).  Run once on warm
+    # and once on cold caches, where the loads arrive late.  Bit-identical to the oracle (all rows of the
+    # small shapes, 200 of the wide ones) with and without accumulators and code sums.
+    b = 64
+    L = synth.draw_levels(fmt, N, K, cfg=94, layer=M + fmt)
+    s_w = synth.draw_scales(fmt, N, cfg=94, layer=M + fmt)
+    x = synth.activations_fp16(94, M, 0, M, K, 5, 30.0)
+    pk = pack_dev(Q, L, s_w, fmt)
+    act = Q.rotate_quant_act(dev(x), b)
+    q_ref, sx_ref = check_act(act, x, b)
+    rows = None if N <= 1000 else np.unique(np.concatenate([np.arange(8), np.random.default_rng(M).choice(N, 200),
+                                                            np.arange(N - 8, N)]))
+    cold = torch.empty(512 << 20, dtype=torch.uint8, device="cuda")
+    first = None
+    for use_sum in (False, True):
+        y, acc = run_linear(Q, pk, act, M, N, use_sum=use_sum)
+        if first is None:
+            first = y
+            check_linear(y, acc, L, q_ref, sx_ref, s_w, rows=rows)
+        for _ in range(2):
+            cold.fill_(1)
+            y2 = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+            Q.linear(pk, act, out=y2, use_sum=use_sum)
+            torch.cuda.synchronize()
+            assert torch.equal(y2.view(torch.int16), first.view(torch.int16))
+        assert torch.equal(y.view(torch.int16), first.view(torch.int16))

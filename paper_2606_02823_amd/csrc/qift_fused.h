@@ -208,26 +208,51 @@ __global__ __launch_bounds__((fused_threads<NTILES, CODES>())) void k_fused_deco
     swq = dev::bload8(srs, wave < T && n_st < N ? (uint32_t)(2 * n_st) : dev::kOutOfRange);
   } else if (wave < 4) {
     // ---- activation waves: rotate and quantize every token into LDS
-    dev::GroupSync<4> sync{ctr, 0u, wait_limit, err};
-    dev::TokenRaw<NTILES> raw;
-    dev::load_token_raw<256, NTILES>(raw, x, K);
-    swq = dev::bload8(srs, wave < T && n_st < N ? (uint32_t)(2 * n_st) : dev::kOutOfRange);
-    if constexpr (NTILES > 1 && !CODES) {
-      // long tokens: the weight waves wait for this before issuing, so the token's loads reach the
-      // memory pipeline ahead of the weight stream (which has time to spare until the codes are in)
-      asm volatile("" ::: "memory");
-      if (lane == 0) __hip_atomic_fetch_add(xflag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    for (int m = 0; m < M; ++m) {
-      dev::TokenRaw<NTILES> cur = raw;
-      if constexpr (NTILES <= 2) {
-        if (m + 1 < M) dev::load_token_raw<256, NTILES>(raw, x + (int64_t)(m + 1) * K, K);   // next token in flight
-      } else {
-        if (m > 0) dev::load_token_raw<256, NTILES>(cur, x + (int64_t)m * K, K);
+    bool staged = false;
+    if constexpr (NTILES == 1 && LC <= 10) {
+      // tokens of up to 1024 elements: one to a wave, all at once (512 x 256 at four tokens 10.3 -> 4.4 us, 2000 x 1024 14.3 -> 5.3:
+      // the four waves took them one after another, most lanes empty)
+      staged = K <= dev::kWaveMaxK && L <= 10;
+      if (staged) {
+        swq = dev::bload8(srs, wave < T && n_st < N ? (uint32_t)(2 * n_st) : dev::kOutOfRange);
+        const int m = wave;
+        if (m < M) {
+          const __amdgpu_buffer_rsrc_t r = dev::make_rsrc(x + (int64_t)m * K, (uint32_t)K * 2u);
+          const uint32_t off = 16 * lane < K ? 32u * lane : dev::kOutOfRange;
+          const uint4 raw[2] = {dev::bload16(r, off), dev::bload16(r, off + 16)};
+          int sum_q;
+          const double A = dev::quant_token_wave<PLANAR>(raw, K, LC > 0 ? LC : L, num, den, xch0 + wave * dev::kWaveXch,
+                                                         act_l + m * Kpad, xbf16 != 0, sum_q);
+          if (lane == 0) {
+            s_scale[m] = (float)((A * (double)num) / denom);
+            red_i[4 * m] = sum_q;
+            red_i[4 * m + 1] = red_i[4 * m + 2] = red_i[4 * m + 3] = 0;
+          }
+        }
       }
-      const double A = dev::quant_token_group<NTILES, LC, PLANAR>(cur, K, L, num, den, xch0, xch1, red_d + 4 * m,
-                                                          red_i + 4 * m, sync, act_l + m * Kpad, xbf16 != 0);
-      if (tid == 0) s_scale[m] = (float)((A * (double)num) / denom);
+    }
+    if (!staged) {
+      dev::GroupSync<4> sync{ctr, 0u, wait_limit, err};
+      dev::TokenRaw<NTILES> raw;
+      dev::load_token_raw<256, NTILES>(raw, x, K);
+      swq = dev::bload8(srs, wave < T && n_st < N ? (uint32_t)(2 * n_st) : dev::kOutOfRange);
+      if constexpr (NTILES > 1 && !CODES) {
+        // long tokens: the weight waves wait for this before issuing, so the token's loads reach the
+        // memory pipeline ahead of the weight stream (which has time to spare until the codes are in)
+        asm volatile("" ::: "memory");
+        if (lane == 0) __hip_atomic_fetch_add(xflag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      for (int m = 0; m < M; ++m) {
+        dev::TokenRaw<NTILES> cur = raw;
+        if constexpr (NTILES <= 2) {
+          if (m + 1 < M) dev::load_token_raw<256, NTILES>(raw, x + (int64_t)(m + 1) * K, K);   // next token in flight
+        } else {
+          if (m > 0) dev::load_token_raw<256, NTILES>(cur, x + (int64_t)m * K, K);
+        }
+        const double A = dev::quant_token_group<NTILES, LC, PLANAR>(cur, K, L, num, den, xch0, xch1, red_d + 4 * m,
+                                                            red_i + 4 * m, sync, act_l + m * Kpad, xbf16 != 0);
+        if (tid == 0) s_scale[m] = (float)((A * (double)num) / denom);
+      }
     }
   } else {
     // ---- weight waves: the first batch of weights (zeros for rows past N and k past K)

@@ -563,6 +563,69 @@ __device__ __forceinline__ double quant_token_group(const TokenRaw<NTILES>& raw,
   return A;
 }
 
+// Rotate + quantize one token of K <= 1024 elements (blocks of up to 1024) by one wave alone: lane l holds
+// elements 16 l .. 16 l + 15, so every exchange stays within the wave (a wave's LDS accesses complete in
+// order: no barrier, only the compiler is kept from reordering them) and a workgroup's waves take a token
+// each.  xch: kWaveXch doubles of this wave's own.  Codes as in quant_token_group; returns A, and the
+// sum of the codes in sum_q.
+constexpr int64_t kWaveMaxK = 1024;
+constexpr int kWaveXch = 1024 + 128;
+
+__device__ __forceinline__ void wave_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <bool PLANAR>
+__device__ __forceinline__ double quant_token_wave(const uint4 (&raw)[2], int K, int L, int num, int den, double* xch,
+                                                   int8_t* dst, bool xbf16, int& sum_q) {
+  const int l = threadIdx.x & 63;
+  double v[16];
+  if (xbf16) unpack_bf16(v, raw);
+  else unpack_fp16(v, raw);
+  reg_stages<16>(v, 0, L < 4 ? L : 4);
+  int w = 0;
+  if (L == 5 || L == 6) {
+    lane_stage<0>(v);
+    if (L == 6) lane_stage<1>(v);
+  } else if (L > 6) {
+    lds_store_w<0>(xch, v, l);
+    wave_order();
+    lds_load_w<4>(xch, v, l);
+    reg_stages<16>(v, 0, (L < 8 ? L : 8) - 4);
+    w = 4;
+    if (L > 8) {   // index bits 8 and 9 are register bits 2 and 3 of window 6
+      wave_order();
+      lds_store_w<4>(xch, v, l);
+      wave_order();
+      lds_load_w<6>(xch, v, l);
+      reg_stages<16>(v, 2, L - 6);
+      w = 6;
+    }
+  }
+  double amax = 0.0;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) amax = fmax(amax, fabs(v[e]));
+  amax = wave_max(amax);   // in lane 0
+  const double A = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(amax)),
+                                    __builtin_amdgcn_readfirstlane(__double2loint(amax)));
+  int q[16], qs = 0;
+  quant16(v, make_qparams(A, num, den), q);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) qs += q[e];   // elements past K are zeros
+  sum_q = wave_sum(qs);
+  if (w == 0) {
+    if (16 * l < K) store_codes<0, PLANAR>(dst, q, l);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = w == 4 ? win_elem<4>(l) + (e << 4) : win_elem<6>(l) + (e << 6);
+      if (i < K) dst[code_pos<PLANAR>(i)] = (int8_t)q[e];
+    }
+  }
+  return A;
+}
+
 template <int NT, int NTILES, bool BF16 = false>
 __device__ __forceinline__ void quant_token(const uint16_t* xr, int64_t K, int L, int num, int den,
                                             double denom, double* lds, double* red_d, int* red_i,

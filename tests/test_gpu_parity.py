@@ -689,3 +689,37 @@ def test_tiled_gemm(Q, fmt, M, N, K):
             torch.cuda.synchronize()
             assert torch.equal(y2.view(torch.int16), first.view(torch.int16))
         assert torch.equal(y.view(torch.int16), first.view(torch.int16))
+
+
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("K,b", [(64, 2), (64, 64), (128, 8), (192, 64), (256, 256), (384, 128), (640, 128), (768, 256),
+                                 (1024, 32), (1024, 512), (1024, 1024), (1088, 64)])
+def test_fused_one_wave_per_token(Q, fmt, K, b):
+    # tokens of up to 1024 elements are rotated by one wave each: every block exponent up to 10, K that
+    # ends inside a wave's window (and 1088, one past the limit), 1 to 4 tokens, a zero token, fp16 and
+    # bf16, the paper's clip ratio; codes, scales, sums, accumulators and y bit-exact
+    N = 72
+    L = synth.draw_levels(fmt, N, K, cfg=93, layer=K + b)
+    s_w = synth.draw_scales(fmt, N, cfg=93, layer=K + b)
+    pk = pack_dev(Q, L, s_w, fmt)
+    for M in (1, 2, 3, 4):
+        x = synth.activations_fp16(93, K + M, 0, M, K, 3, 30.0)
+        if M == 3:
+            x[1] = 0
+        act = Q.alloc_act(M, K)
+        acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+        y = Q.rotate_quant_linear(pk, dev(x), b, acc_out=acc, act_out=act)
+        torch.cuda.synchronize()
+        q_ref, sx_ref = check_act(act, x, b)
+        check_linear(y, acc, L, q_ref, sx_ref, s_w)
+        y = Q.rotate_quant_linear(pk, dev(x), b, clip=(9, 10), acc_out=acc)
+        torch.cuda.synchronize()
+        q_ref, sx_ref, _, _ = quant.act_quant(x, b, (9, 10))
+        check_linear(y, acc, L, q_ref, sx_ref, s_w)
+    xb = _bf16_any(np.random.default_rng(K + b), 4, K, b)
+    aq = Q.alloc_act(4, K)
+    acc = torch.empty((4, N), dtype=torch.int32, device="cuda")
+    Q.rotate_quant_linear(pk, xb.cuda(), b, acc_out=acc, act_out=aq)
+    torch.cuda.synchronize()
+    q_ref, _ = check_act_bf16(aq, xb.float().numpy(), b)
+    assert np.array_equal(host(acc), olin.int_dot(L, q_ref))

@@ -65,6 +65,8 @@ SPEC_BF16 = 1 << 16   # QIFT_SPEC_BF16: the tokens are bf16 values
 
 
 def spec(K: int, block: int, clip=(1, 1), bf16: bool = False) -> HadamardSpec:
+    if clip == (1, 1) and not bf16:
+        return HadamardSpec(K, block, 0)
     return HadamardSpec(K, block, clip_flags(*clip) | (SPEC_BF16 if bf16 else 0))
 
 
@@ -143,11 +145,20 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():
+        # the handle of the current device's current stream without building a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
+# One expression where all is well: a call on one small linear takes longer on the host than on the GPU
+# (512 x 256 at four tokens, one call after another: 9.5 -> 6.5 us of host time, 2.5 us of it the stream
+# handle and 1.0 us these checks, against 4.4 us on the GPU).
 def _dev(t: torch.Tensor, dtype, shape, name):
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:

@@ -215,3 +215,19 @@ def test_kv4_attention_workspace_reuse(Q):
             err = np.abs(y.cpu().numpy().astype(np.float64) - ref).max(axis=-1) / np.abs(ref).max(axis=-1)
             print(f"reused workspace B={B} T={T} call {rep}: max rel err {err.max():.2e}")
             assert err.max() <= TOL, (B, T, rep, err.max())
+
+
+@pytest.mark.parametrize("groups", [1, 5, 16, 17, 262143, 262144 + 53])
+def test_kv4_quant_group_counts(Q, groups):
+    # one step of 16 groups to a workgroup below 262144 groups, four above (the last workgroup ends inside
+    # a step); values on the rounding thresholds of their own scale are among the seeded ones
+    rng = np.random.default_rng(groups)
+    x = groups_fp16(rng, groups)
+    n = min(groups, 64)
+    x[:n] = (np.round(rng.uniform(-15, 15, (n, 128))) * 0.5).astype(np.float16)   # many exact halves of a step
+    c = Q.kv4_quant(torch.from_numpy(x).cuda())
+    torch.cuda.synchronize()
+    q_ref, s_ref, z_ref = okv4.kv4_quant(x)
+    assert np.array_equal(c.scales.cpu().numpy().view(np.uint32), s_ref.view(np.uint32))
+    assert np.array_equal(c.zeros.cpu().numpy(), z_ref)
+    assert np.array_equal(c.codes.cpu().numpy(), okv4.pack_nibbles(q_ref))

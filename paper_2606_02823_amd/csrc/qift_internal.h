@@ -61,6 +61,11 @@ hipError_t launch_linear(int fmt, const uint32_t* packed, const uint16_t* scales
 hipError_t launch_gemm32(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                          const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s);
 
+// Linear on codes for batches of up to 64 tokens, K cut into a slice per wave (qift_batch.hip).
+constexpr int64_t kBatchMaxM = 64;
+hipError_t launch_batch(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
+                        const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s);
+
 // Fused rotation + quantization + linear for a few decode tokens, one launcher
 // per weight format (qift_fused_<fmt>.hip).
 #define QIFT_FUSED_LAUNCHER(NAME)                                                                          \

@@ -560,15 +560,45 @@ inline GemmSplit gemm_split_plan(int fmt, int64_t N, int64_t M, int64_t K) {
 // to 64 of them (4096 x 4096, split against not, us: 12.4 / 16.5 at 100 tokens, 14.5 / 16.5 at 256, but
 // 19 / 16.6 at 300 and 27 / 17.8 at 600; 12288 x 4096 19.9 / 17.5 at 100), W4 up to 96 (6144 x 4096 21.5 /
 // 22.3 at 192, 24 / 22.3 at 300).  Wide linears of a short K do not split where the GEMM takes them
-// (gemm_wide).  A long K splits wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at
+// (gemm_wide); up to 64 tokens most linears go to the batch kernel first (take_batch).  A long K splits wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at
 // 1024).
 inline bool gemm_wide(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
-  // From 33 tokens on a wide linear (gate|up) takes the tiled GEMM rather than the skinny kernel, whose
-  // workgroups each read all M x K codes (28672 x 4096 at 33 / 64 tokens: W2 22.9 -> 17.3 / 28.2 -> 18.6 us,
-  // W4 36.6 -> 25.6 / 46.8 -> 27.6), and unsplit (W2 20.0 -> 17.1 / 24.7 -> 18.0 at 33 / 64 with a
-  // workspace), except a long K and, below 49 tokens, W4 with a workspace (25.0 -> 25.6, 22.8 -> 24.2 at 33).
+  // From 33 tokens on a wide linear that the batch kernel leaves (take_batch) runs the tiled GEMM rather than
+  // the skinny kernel, whose workgroups each read all M x K codes (28672 x 4096 at 33 / 64 tokens: W2 22.9 ->
+  // 17.3 / 28.2 -> 18.6 us), and unsplit unless K is long.
   if (N < kSplitWideMinN || M < kSplitWideMinM) return false;
-  return !ws || (K < 8192 && (fmt != FMT_W4 || M > 48));
+  return !ws || K < 8192;
+}
+// The batch kernel (K cut into a slice per wave), up to 64 tokens.  Its time hardly grows with the tokens,
+// so it is the faster from some count on; where, by what it replaces (us at 4096-k unless said, old / batch):
+//   17-64 tokens, the skinny kernel (workgroups that read all codes), its split and the split GEMM:
+//     wide (N >= 16384): W2 16.6 / 14.4 at 17, 22016 rows 17.8 / 12.2 at 32 and 18.2 / 16.3 at 64, W4 21.4 /
+//     16.2 at 24; not W2 of more than 24576 rows from 33 tokens on, the tiled GEMM's (28672: 18.6 / 20.2);
+//     others: 12288 rows 8.7 / 8.3 at 17, W4 23.4 / 12.5 at 64; 4096 rows 6.5 / 6.3 at 24 (5.9 / 6.2 at 17) and
+//     10.8 / 6.6 at 64; a short K (2048) from 48 tokens, W4 6.0 / 5.7 (4.8 / 5.2 at 32).  W4 of a long K with a
+//     workspace stays with the split GEMM below 33 tokens (4096 x 11008 12.4 / 12.9 at 24);
+//   5-16 tokens, the decode kernel on codes: wide and K > 4096 (16384 x 8192, whose one 16-row tile per
+//     workgroup takes four rounds: 23.4 / 13.4 at 9, W4 29.3 / 21.6 at 12); W2 of 4097-8192 rows from 12 (6.9 /
+//     6.4); and from 9 where the codes exceed its LDS and no workspace lets it split (4096 x 14336 at 16: 14.5 /
+//     11.6; K = 20480 15.0 / 13.6 at 9);
+//   K > 16384 from 17 tokens on, the prefill GEMM (4096 x 20480 at 24: 70 / 14.7).
+inline bool take_batch(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
+  const bool w4 = fmt == FMT_W4;
+  if (M > kBatchMaxM || M < 5) return false;
+  if (M > kCodesMaxM) {
+    if (K > kSkinnyMaxK) return true;
+    if (N >= kSplitWideMinN) return K >= 2048 && (w4 || M <= 32 || N <= 24576);
+    if (M >= 48) return K >= 2048;
+    if (K < 4096) return false;
+    if (N > 4096) return true;
+    if (w4) return K > 8192 ? !ws || M < kSplitWideMinMW4 || M >= 33 : M >= 24;
+    return M >= 24 || N <= 2048;
+  }
+  if (N >= kSplitWideMinN && K > 4096) return !w4 || M >= 9;
+  if (!w4 && K == 4096 && N > 4096 && N <= 8192) return M >= 12;
+  const size_t cs = fmt == FMT_MNZ ? codes_shmem_mnz(M, N, K) : fmt == FMT_POT ? codes_shmem_pot(M, N, K)
+                                                                               : codes_shmem_w4(M, N, K);
+  return (cs == 0 || cs > 160 * 1024) && M >= (w4 ? 12 : 9) && !(ws && skinny_workspace(fmt, N, K, M) != 0);
 }
 inline bool take_split(const GemmSplit& p, int fmt, int64_t N, int64_t M, int64_t K) {
   if (p.S < 2) return false;
@@ -654,6 +684,7 @@ template <int FMT>
 hipError_t launch_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                       const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
                       hipStream_t s) {
+  if (take_batch(FMT, N, M, K, ws != nullptr)) return launch_batch(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
   if (ws) {
     const GemmSplit p = gemm_split_plan(FMT, N, M, K);
     if (take_split(p, FMT, N, M, K))

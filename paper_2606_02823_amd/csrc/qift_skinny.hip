@@ -21,7 +21,8 @@
 // tokens), so a linear with K > 4096 and few 16-row tiles (down) takes four tiles per workgroup and
 // gives each workgroup a range of K instead: workgroup (x, z) writes its int32 partial sums of tile
 // group x over unit range z to the workspace, and the second pass (qift_split.h) adds the ranges (integers: exact in any
-// order) and applies the epilogue (down at 64 tokens: 28.9 -> 16.4 us).
+// order) and applies the epilogue (down at 17 tokens: 11.7 -> 10.3 us; from 24 tokens on the batch kernel
+// takes such linears).
 #include "qift_fwht.h"
 #include "qift_internal.h"
 #include "qift_mma.h"
@@ -327,8 +328,8 @@ hipError_t launch_split_fmt(const SkSplit& p, const uint32_t* P, const uint16_t*
                             const int8_t* act, const float* sx, const int32_t* asum, int64_t M, uint16_t* y,
                             int32_t* acc_out, void* ws, hipStream_t s) {
 #define QIFT_SPLIT(T_, TT_) launch_split_t<FMT, T_, TT_>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s)
-  if (M <= 32) return M <= 16 ? QIFT_SPLIT(4, 1) : QIFT_SPLIT(4, 2);
-  return QIFT_SPLIT(4, 4);
+  if (M > 32) return hipErrorInvalidValue;   // the batch kernel's
+  return M <= 16 ? QIFT_SPLIT(4, 1) : QIFT_SPLIT(4, 2);
 #undef QIFT_SPLIT
 }
 
@@ -348,7 +349,7 @@ hipError_t launch_skinny_ws(int fmt, const uint32_t* P, const uint16_t* sw, int6
                             const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
                             hipStream_t s) {
   const SkSplit p = split_plan(fmt, N, K, M);
-  if (ws == nullptr || p.S == 0) return launch_skinny(fmt, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+  if (ws == nullptr || p.S == 0 || M > 32) return launch_skinny(fmt, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
   switch (fmt) {
     case FMT_MNZ: return launch_split_fmt<FMT_MNZ>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
     case FMT_POT: return launch_split_fmt<FMT_POT>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);

@@ -723,3 +723,40 @@ def test_fused_one_wave_per_token(Q, fmt, K, b):
     torch.cuda.synchronize()
     q_ref, _ = check_act_bf16(aq, xb.float().numpy(), b)
     assert np.array_equal(host(acc), olin.int_dot(L, q_ref))
+
+
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("M,N,K", [(17, 4100, 4096), (24, 520, 4160), (32, 8200, 4096), (33, 999, 4736), (64, 4096, 2048),
+                                   (48, 40, 2112), (64, 12288, 4096), (12, 4160, 4096), (5, 16384, 4160), (9, 16400, 4672),
+                                   (16, 70, 16448), (40, 33, 20480), (20, 16385, 2048), (24, 25000, 2176),
+                                   (64, 24576, 2048)])
+def test_batch_linear(Q, fmt, M, N, K):
+    # The batch kernel's edges: one to four 32-row tiles a workgroup (N up to and past 8192, 16384, 24576),
+    # one and two token tiles (and two workgroups of one where N <= 4096), slices of K that end inside a step
+    # or a line group, slices past K (K = 2048 and 2112 over 4 and 8 waves), odd counts of line groups; rows
+    # and tokens that end inside a tile.  Warm and cold caches (late loads).  Bit-identical to the oracle,
+    # with and without accumulators, code sums and a workspace.
+    b = 64
+    L = synth.draw_levels(fmt, N, K, cfg=92, layer=M + fmt)
+    s_w = synth.draw_scales(fmt, N, cfg=92, layer=M + fmt)
+    x = synth.activations_fp16(92, M, 0, M, K, 7, 30.0)
+    pk = pack_dev(Q, L, s_w, fmt)
+    act = Q.rotate_quant_act(dev(x), b)
+    q_ref, sx_ref = check_act(act, x, b)
+    rows = None if N <= 1000 else np.unique(np.concatenate([np.arange(8), np.random.default_rng(N).choice(N, 150),
+                                                            np.arange(N - 40, N)]))
+    need = Q.workspace_bytes(pk, M)
+    cold = torch.empty(512 << 20, dtype=torch.uint8, device="cuda")
+    first = None
+    for ws in (None, torch.empty(need, dtype=torch.uint8, device="cuda") if need else None):
+        for use_sum in (False, True):
+            y, acc = run_linear(Q, pk, act, M, N, use_sum=use_sum, workspace=ws)
+            if first is None:
+                first = y
+                check_linear(y, acc, L, q_ref, sx_ref, s_w, rows=rows)
+            cold.fill_(1)
+            y2 = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+            Q.linear(pk, act, out=y2, use_sum=use_sum, workspace=ws)
+            torch.cuda.synchronize()
+            assert torch.equal(y.view(torch.int16), first.view(torch.int16))
+            assert torch.equal(y2.view(torch.int16), first.view(torch.int16))

@@ -7,8 +7,11 @@
 // and waits only on its own load counter.  RJ is chosen so that the grid is about one workgroup per CU:
 // the weights are read once, each CU reads the M x K codes once, and the time hardly grows with the tokens.
 // What bounds it at these sizes is latency: launch, the first loads from HBM, a few steps (a 4096-k row is
-// 32 steps over 4 or 8 waves), the sum of the slices.  Eight waves where their registers allow (32 RJ TC
-// accumulators each), four otherwise.
+// 32 steps over 4 or 8 waves), the sum of the slices, and the address unit, which takes about 55 cycles for
+// each kilobyte of codes: so the loads of a step cover 16, 32, 48 or 64 tokens (NA; 4096 x 14336 at 16 tokens
+// 11.5 -> 10.2 us against 32), and RJ is as large as the grid allows.  Eight waves where their registers allow (32 RJ TC
+// accumulators each), four otherwise.  Four line groups of weights in flight instead of two measured slower
+// (12288 x 4096 at 16 tokens 8.2 -> 9.1 us).
 // us, before (skinny kernel, its split over K, the split GEMM) -> now: W4 12288 x 4096 at 37 tokens 19.0 ->
 // 12.1, 22016 x 4096 23.5 -> 19.6; W2 6144 x 4096 at 64 11.9 -> 7.9, 4096 x 14336 15.7 -> 13.1 (without a
 // workspace 29.8 -> 12.8), 28672 x 4096 at 24 17.7 -> 14.3 (its 29 MB take 5.6 us at a large copy's rate).
@@ -33,7 +36,7 @@ constexpr int line_steps() { return FMT == FMT_W4 ? 2 : 4; }   // steps in 128 b
 // slot of 16-byte column c of activation row r (8 and 16 consecutive rows spread over the banks)
 __device__ __forceinline__ int slot(int r, int c) { return c ^ (((r >> 1) & 7) ^ ((r & 1) << 2)); }
 
-template <int FMT, int RJ, int TC, int NWV, bool SUMQ>
+template <int FMT, int RJ, int NA, int NWV, bool SUMQ>
 __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_batch(const uint32_t* __restrict__ P,
                                                              const uint16_t* __restrict__ sw, int N, int K,
                                                              const int8_t* __restrict__ act,
@@ -41,7 +44,9 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_batch(const uint32_t* __r
                                                              const int32_t* __restrict__ asum, int M,
                                                              uint16_t* __restrict__ y, int32_t* __restrict__ acc_out) {
   constexpr int NB = FMT == FMT_W4 ? 2 : 1, LS = line_steps<FMT>();
-  constexpr int NA = 4 * TC;            // direct-to-LDS loads of a step (1 KB, 8 tokens each)
+  // NA: direct-to-LDS loads of a step, 1 KB and 8 tokens each (tokens past them: whatever the stage holds,
+  // in outputs that are not stored)
+  constexpr int TC = (NA + 3) / 4;
   constexpr int NW = RJ * NB * LS;      // weight loads of a line group
   constexpr int BUF = 4096 * TC;        // bytes of a wave's stage
   __shared__ __align__(16) int8_t lds0[NWV * BUF];
@@ -282,15 +287,16 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_batch(const uint32_t* __r
   }
 }
 
-template <int FMT, int RJ, int TC, int NWV>
+template <int FMT, int RJ, int NA, int NWV>
 hipError_t launch_t(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act, const float* sx,
                     const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s) {
+  constexpr int TC = (NA + 3) / 4;
   const dim3 grid((unsigned)((N + 32 * RJ - 1) / (32 * RJ)), (unsigned)((M + 32 * TC - 1) / (32 * TC)));
   if (asum)
-    hipLaunchKernelGGL((k_batch<FMT, RJ, TC, NWV, false>), grid, dim3(64 * NWV), 0, s, P, sw, (int)N, (int)K, act, sx,
+    hipLaunchKernelGGL((k_batch<FMT, RJ, NA, NWV, false>), grid, dim3(64 * NWV), 0, s, P, sw, (int)N, (int)K, act, sx,
                        asum, (int)M, y, acc_out);
   else
-    hipLaunchKernelGGL((k_batch<FMT, RJ, TC, NWV, true>), grid, dim3(64 * NWV), 0, s, P, sw, (int)N, (int)K, act, sx,
+    hipLaunchKernelGGL((k_batch<FMT, RJ, NA, NWV, true>), grid, dim3(64 * NWV), 0, s, P, sw, (int)N, (int)K, act, sx,
                        asum, (int)M, y, acc_out);
   return hipGetLastError();
 }
@@ -302,17 +308,29 @@ hipError_t launch_f(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
   const int64_t rj = (N + 32 * 256 - 1) / (32 * 256);   // rows for about one workgroup per CU
   // up to 4096 rows two token tiles share the chip (4096 x 4096 at 64 tokens 7.4 -> 6.6 us, 4096 x 14336
   // 16.1 -> 13.1)
-#define QIFT_B(RJ_, TC_, NWV_) launch_t<FMT, RJ_, TC_, NWV_>(P, sw, N, K, act, sx, asum, M, y, acc_out, s)
-  if (M <= 32 || N <= 4096) {
-    if (rj <= 1) return QIFT_B(1, 1, 8);
-    if (rj == 2) return QIFT_B(2, 1, 8);
-    if (rj == 3) return QIFT_B(3, 1, 4);
-    return QIFT_B(4, 1, 4);
+#define QIFT_B(RJ_, NA_, NWV_) launch_t<FMT, RJ_, NA_, NWV_>(P, sw, N, K, act, sx, asum, M, y, acc_out, s)
+  if (M <= 16) {
+    if (rj <= 1) return QIFT_B(1, 2, 8);
+    if (rj == 2) return QIFT_B(2, 2, 8);
+    if (rj == 3) return QIFT_B(3, 2, 4);
+    return QIFT_B(4, 2, 4);
   }
-  if (rj <= 1) return QIFT_B(1, 2, 4);
-  if (rj == 2) return QIFT_B(2, 2, 4);
-  if (rj == 3) return QIFT_B(3, 2, 4);
-  return QIFT_B(4, 2, 4);
+  if (M <= 32 || N <= 4096) {
+    if (rj <= 1) return QIFT_B(1, 4, 8);
+    if (rj == 2) return QIFT_B(2, 4, 8);
+    if (rj == 3) return QIFT_B(3, 4, 4);
+    return QIFT_B(4, 4, 4);
+  }
+  if (M <= 48) {
+    if (rj <= 1) return QIFT_B(1, 6, 4);
+    if (rj == 2) return QIFT_B(2, 6, 4);
+    if (rj == 3) return QIFT_B(3, 6, 4);
+    return QIFT_B(4, 6, 4);
+  }
+  if (rj <= 1) return QIFT_B(1, 8, 4);
+  if (rj == 2) return QIFT_B(2, 8, 4);
+  if (rj == 3) return QIFT_B(3, 8, 4);
+  return QIFT_B(4, 8, 4);
 #undef QIFT_B
 }
 

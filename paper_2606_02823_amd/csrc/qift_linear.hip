@@ -578,9 +578,11 @@ inline bool gemm_wide(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
 //     10.8 / 6.6 at 64; a short K (2048) from 48 tokens, W4 6.0 / 5.7 (4.8 / 5.2 at 32).  W4 of a long K with a
 //     workspace stays with the split GEMM below 33 tokens (4096 x 11008 12.4 / 12.9 at 24);
 //   5-16 tokens, the decode kernel on codes: wide and K > 4096 (16384 x 8192, whose one 16-row tile per
-//     workgroup takes four rounds: 23.4 / 13.4 at 9, W4 29.3 / 21.6 at 12); W2 of 4097-8192 rows from 12 (6.9 /
-//     6.4); and from 9 where the codes exceed its LDS and no workspace lets it split (4096 x 14336 at 16: 14.5 /
-//     11.6; K = 20480 15.0 / 13.6 at 9);
+//     workgroup takes four rounds: 23.4 / 13.4 at 9, W4 29.3 / 20.6 at 12); W2 of at most 16384 rows from 12
+//     tokens (at 16: 6144 rows 7.3 / 5.7, 4096 6.4 / 5.5, 12288 8.3 / 7.9, 4096 x 11008 9.3 / 8.6), 4097-8192
+//     rows from 9 (6.1 / 5.6 at 8); W4 from 15 tokens, wide or at most 4096 rows (28672 22.2 / 20.1, 4096 x
+//     11008 13.6 / 11.2, 4096 6.5 / 6.3 at 16, but 12288 9.0 / 9.3); and from 9 where the codes exceed its LDS
+//     (4096 x 14336 at 16: 14.5 / 10.2, with a workspace 10.3 / 10.2; K = 20480 15.0 / 13.6 at 9);
 //   K > 16384 from 17 tokens on, the prefill GEMM (4096 x 20480 at 24: 70 / 14.7).
 inline bool take_batch(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
   const bool w4 = fmt == FMT_W4;
@@ -595,7 +597,8 @@ inline bool take_batch(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
     return M >= 24 || N <= 2048;
   }
   if (N >= kSplitWideMinN && K > 4096) return !w4 || M >= 9;
-  if (!w4 && K == 4096 && N > 4096 && N <= 8192) return M >= 12;
+  if (K >= 4096 && M >= 15 && w4 && (N >= kSplitWideMinN || N <= 4096)) return true;
+  if (K >= 4096 && !w4 && N <= kSplitWideMinN && M >= (N > 4096 && N <= 8192 ? 9 : 12)) return true;
   const size_t cs = fmt == FMT_MNZ ? codes_shmem_mnz(M, N, K) : fmt == FMT_POT ? codes_shmem_pot(M, N, K)
                                                                                : codes_shmem_w4(M, N, K);
   return (cs == 0 || cs > 160 * 1024) && M >= (w4 ? 12 : 9) && !(ws && skinny_workspace(fmt, N, K, M) != 0);

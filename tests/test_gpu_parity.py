@@ -726,7 +726,7 @@ def test_fused_one_wave_per_token(Q, fmt, K, b):
 
 
 @pytest.mark.parametrize("fmt", FMTS)
-@pytest.mark.parametrize("M,N,K", [(17, 4100, 4096), (24, 520, 4160), (32, 8200, 4096), (33, 999, 4736), (64, 4096, 2048),
+@pytest.mark.parametrize("M,N,K", [(17, 4100, 4096), (16, 4096, 4096), (15, 300, 4736), (9, 6200, 4096), (24, 520, 4160), (32, 8200, 4096), (33, 999, 4736), (64, 4096, 2048),
                                    (48, 40, 2112), (64, 12288, 4096), (12, 4160, 4096), (5, 16384, 4160), (9, 16400, 4672),
                                    (16, 70, 16448), (40, 33, 20480), (20, 16385, 2048), (24, 25000, 2176),
                                    (64, 24576, 2048)])

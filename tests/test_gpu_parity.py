@@ -332,6 +332,30 @@ def test_rotate_quant_act_tile_parallel(Q, M, K, b):
     check_act(act, x, b)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("M,K,b", [(257, 12352, 64), (257, 16384, 4096), (300, 14336, 256), (259, 12352, 2),
+                                   (261, 13312, 1024), (2049, 14336, 2048)])
+def test_rotate_quant_act_two_groups(Q, M, K, b, bf16):
+    # past 256 tokens a token of four 4096-tiles is rotated by two groups of waves, two tiles each: every
+    # compiled block exponent (and others), a last tile of a few elements, full tiles; exact as elsewhere
+    x = synth.activations_fp16(95, M, b, M, K, max(1, K // 100), 30.0)
+    x[1] = 0                                                # all-zero token
+    x[2] = 0
+    x[2, K - 1] = 3.0                                       # only the last tile holds anything
+    tokens = np.array([0, 1, 2, 3, 255, 256, M - 2, M - 1])
+    if bf16:
+        x = torch.from_numpy(x).to(torch.bfloat16)
+        x[3, K - 64:] *= 2.0 ** 90                          # beyond fp16's range
+        act = Q.rotate_quant_act(x.cuda(), b)
+        q_ref, sx_ref, sum_ref, _ = quant.act_quant_staged(x[tokens].float().numpy(), b, (1, 1))
+    else:
+        act = Q.rotate_quant_act(dev(x), b)
+        q_ref, sx_ref, sum_ref, _ = quant.act_quant(x[tokens], b, (1, 1))
+    assert np.array_equal(host(act.q)[tokens], q_ref)
+    assert np.array_equal(host(act.scale)[tokens].view(np.uint32), sx_ref.view(np.uint32))
+    assert np.array_equal(host(act.sum)[tokens], sum_ref)
+
+
 def test_rotate_quant_act_exact_ties(Q):
     u = 2.0 ** -10
     pairs = [(9.5, 4.5), (10.5, 3.5), (7.5, 6.5), (8.5, 5.5), (4.5, 9.5)]

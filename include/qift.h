@@ -294,8 +294,9 @@ int qift_rotate_quant_act_bf16(const uint16_t *x, int64_t M, qift_hadamard_spec 
  *   out        out: fp16 y [M][N].
  * The kernels run the MFMA on the raw 2-bit codes and add the exact level
  * correction from the per-token sum of the codes, which they compute from
- * the act_q tiles they stage.  M <= 64 runs the skinny decode kernel; larger
- * M runs the tiled prefill kernel; both give identical results.
+ * the act_q tiles they stage.  Up to 16 tokens the decode kernel on codes, up
+ * to 64 the batch kernel (from 9 to 15 tokens on for most weights) or the
+ * skinny one, beyond the tiled prefill GEMM; all give identical results.
  */
 int qift_w2a4_linear(const qift_packed_w *w, const int8_t *act_q, const float *act_scale,
                      int64_t M, uint16_t *out, qift_stream_t stream);
@@ -308,18 +309,18 @@ int qift_w2a4_linear(const qift_packed_w *w, const int8_t *act_q, const float *a
  *              output: it is taken as is).  NULL: summed in the kernel.
  *   acc_out    out, nullable: int32 [M][N], the exact accumulators.
  *   workspace, workspace_bytes   optional device scratch (16-byte aligned).
- *              NULL / 0: no linear is split over K.  With at least
- *              qift_workspace_bytes(w, M) bytes, where that is not 0 (MNZ
- *              and PoT weights):
- *                M > 64 (and from M = 33 on N >= 4096 with K > 4096), where
- *                the GEMM's 256-row x 64-token tiles are few for the length of
- *                K: the int8 GEMM split over K, int32 partial sums of each
- *                K-range in the workspace, then added and the epilogue
- *                applied; else the unsplit GEMM;
- *                M <= 64 otherwise (K > 4096, few 16-row tiles; up to 16 tokens only
- *                where the codes exceed the decode kernel's LDS): the decode
- *                linear is split over K, int32 partial sums of each K-range in
- *                the workspace, then added and the epilogue applied.
+ *              NULL / 0: no linear is split over K in a second launch.  With
+ *              at least qift_workspace_bytes(w, M) bytes, where that is not 0
+ *              (MNZ and PoT weights):
+ *                M > 64, where the GEMM's tiles are few for the length of K:
+ *                the int8 GEMM split over K, int32 partial sums of each K-range
+ *                in the workspace, then added and the epilogue applied; else
+ *                the unsplit GEMM;
+ *                M <= 64, where the batch kernel does not take the linear: the
+ *                same split GEMM from M = 33 on for wide or long weights, else
+ *                (K > 4096, few 16-row tiles; up to 16 tokens only where the
+ *                codes exceed the decode kernel's LDS) the decode linear split
+ *                over K in the same way.
  *              Either way the results are bit-identical.  A non-zero size
  *              below the query is QIFT_ERR_WORKSPACE.  The workspace is
  *              overwritten.
@@ -561,8 +562,8 @@ int qift_kv4_attention_decode_noalloc(const uint16_t *q, int64_t B, int32_t Hq, 
                                       const uint8_t *k_zeros, const uint8_t *v_codes, const float *v_scales,
                                       const uint8_t *v_zeros, uint16_t *out, qift_stream_t stream);
 
-/* Workspace bytes that the _ex calls use for this weight and M, 0 where none is used (host
- * query).  N4 = N rounded up to 4; T = ceil(N / 256) * ceil(M / 64) prefill tiles; a count S of
+/* Workspace bytes that the _ex calls ask for with this weight and M, 0 where none is used (host
+ * query); the batch kernel and the unsplit GEMM accept the workspace and leave it alone.  N4 = N rounded up to 4; T = ceil(N / 256) * ceil(M / 64) prefill tiles; a count S of
  * K-ranges is recounted once the ranges are sized (ranges of ceil(steps / S) steps).
  *   M > 64, and from M = 33 (W4: 24) on N >= 16384 or N >= 4096 with K > 4096: the int8 GEMM split
  *     over S = min(ceil(512 / T), floor(512 / T), floor(steps / s0)) K-ranges when that is at least S0

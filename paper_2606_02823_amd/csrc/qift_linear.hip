@@ -560,8 +560,8 @@ inline GemmSplit gemm_split_plan(int fmt, int64_t N, int64_t M, int64_t K) {
 // to 64 of them (4096 x 4096, split against not, us: 12.4 / 16.5 at 100 tokens, 14.5 / 16.5 at 256, but
 // 19 / 16.6 at 300 and 27 / 17.8 at 600; 12288 x 4096 19.9 / 17.5 at 100), W4 up to 96 (6144 x 4096 21.5 /
 // 22.3 at 192, 24 / 22.3 at 300).  Wide linears of a short K do not split where the GEMM takes them
-// (gemm_wide); up to 64 tokens most linears go to the batch kernel first (take_batch).  A long K splits wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at
-// 1024).
+// (gemm_wide); up to 64 tokens most linears go to the batch kernel first (take_batch).  A long K splits
+// wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at 1024).
 inline bool gemm_wide(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
   // From 33 tokens on a wide linear that the batch kernel leaves (take_batch) runs the tiled GEMM rather than
   // the skinny kernel, whose workgroups each read all M x K codes (28672 x 4096 at 33 / 64 tokens: W2 22.9 ->

@@ -154,20 +154,23 @@ __global__ __launch_bounds__(256 * G) void k_act_wide(const uint16_t* __restrict
 #pragma unroll
   for (int k = 1; k < 4 * G; ++k) A = fmax(A, red_d[k]);
   const dev::QuantParams p = dev::make_qparams(A, num, den);
+  int q[TPG][16];
   int qs = 0;
+#pragma unroll
+  for (int i = 0; i < TPG; ++i) {
+    dev::quant16(v[i], p, q[i]);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) qs += q[i][e];
+  }
   // the codes in natural order through the group's exchange buffer (its exchange reads are done
   // once every wave of the group has passed the wave barrier), then 16 bytes per thread and tile
   gs();
   int8_t* codes = reinterpret_cast<int8_t*>(xch);
 #pragma unroll
   for (int i = 0; i < TPG; ++i) {
-    int q[16];
-    dev::quant16(v[i], p, q);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) qs += q[e];
-    if (wend == 0) dev::store_codes<0>(codes + i * S::T, q, t);
-    else if (wend == 4) dev::store_codes<4>(codes + i * S::T, q, t);
-    else dev::store_codes<8>(codes + i * S::T, q, t);
+    if (wend == 0) dev::store_codes<0>(codes + i * S::T, q[i], t);
+    else if (wend == 4) dev::store_codes<4>(codes + i * S::T, q[i], t);
+    else dev::store_codes<8>(codes + i * S::T, q[i], t);
   }
   gs();
 #pragma unroll

@@ -30,7 +30,7 @@
 //   took about 10 us, at once 6.9).
 //   Beyond, latency between the exchanges bounds the kernel, so what counts is waves per SIMD: a
 //   four-tile token in one group of waves holds 128 fp64 registers' worth of values per thread (199
-//   VGPRs, 2 waves per SIMD), in two groups of two tiles half of that (126, 4 waves).  14336 wide,
+//   VGPRs, 2 waves per SIMD), in two groups of two tiles half of that (117, 4 waves).  14336 wide,
 //   b = 2048, 2048 tokens: 45.4 us in one group, 39.0 in two, 50.6 in four (a fourth of whose last
 //   tile is padding that holds a whole group); 512 tokens: 14.5, 13.3, 15.0; 257: 12.5, 11.4, 12.8.
 //   Three tiles stay with k_act_tokens there: a second group would rotate one tile while the first

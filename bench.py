@@ -478,18 +478,11 @@ def lut_decode(torch, qift, synth, min_bytes=1 << 29, reps=10):
                         "random 2-bit codes (the kernel's work does not depend on them)", "rows": rows}
 
 
-FP64_VECTOR_PEAK_TFLOPS = 78.6
-# per candidate and weight, fp64: the threshold test fma(-2.5, s, |w|) (2 flops), s * level, w - s * level,
-# d * d and the add into the error sum (the scale search's inner loop; there is no division in it)
-POT_FLOPS_PER_WEIGHT = 64 * 6
-
-
 def weight_quantizer(torch, qift, synth, reps=5):
     """The GPU weight quantizer on one LLaMA-3.1-8B layer (its 7 linears, 218M fp32 weights) per
     format: rotation, per-row scale and levels (the offline step before packing; hipGraph replays,
-    weights resident).  MNZ and W4 move 4 B in + 1 B out per weight (HBM roofline); the PoT scale
-    search is fp64 arithmetic, priced at 6 flops per candidate and weight against the fp64 vector
-    peak."""
+    weights resident).  Every format is priced at the 4 B read and 1 B written per weight (HBM
+    roofline)."""
     c = synth.CONFIGS[2]
     dev = torch.device("cuda")
     gen = torch.Generator(device=dev)
@@ -518,13 +511,8 @@ def weight_quantizer(torch, qift, synth, reps=5):
         gbs = (5 * weights + 2 * rows) / dt / 1e9
         rec = {"ms_per_layer": round(dt * 1e3, 3), "gweights_per_s": round(weights / dt / 1e9, 2),
                "GBs": round(gbs, 1), "pct_hbm_peak": round(100 * gbs / HBM_PEAK_GBS, 2)}
-        if fmt == qift.W2_POT:
-            tf = POT_FLOPS_PER_WEIGHT * weights / dt / 1e12
-            rec["roofline"] = {"bound": "alu", "achieved": round(tf, 2), "peak": FP64_VECTOR_PEAK_TFLOPS,
-                               "unit": "TFLOP/s", "frac": round(tf / FP64_VECTOR_PEAK_TFLOPS, 4)}
-        else:
-            rec["roofline"] = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                               "frac": round(gbs / HBM_PEAK_GBS, 4)}
+        rec["roofline"] = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                           "frac": round(gbs / HBM_PEAK_GBS, 4)}
         out[name] = rec
     del mats
     return out

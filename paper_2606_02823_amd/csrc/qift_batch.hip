@@ -18,6 +18,7 @@
 #include "qift_fwht.h"   // buffer-load helpers
 #include "qift_internal.h"
 #include "qift_mma.h"
+#include "qift_waits.h"
 
 #include <type_traits>
 
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_batch(const uint32_t* __r
   auto step = [&](int kt, int8_t* own, const int8_t* nxt, const uint4 (&w)[RJ][NB], auto out) {
     constexpr int OUT = decltype(out)::value;
     issue_a(kt + kNS, own);
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (OUT & 15) | ((OUT >> 4) << 14));
+    __builtin_amdgcn_s_waitcnt(waits::encode(OUT, false));
     __builtin_amdgcn_sched_barrier(0);
     read_b(bn, nxt);
     __builtin_amdgcn_sched_barrier(0);
@@ -189,16 +190,17 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_batch(const uint32_t* __r
     __builtin_amdgcn_sched_barrier(0);
   };
   // The wait of step k is for the activations of step k + 1, sent at step k - 3: those of steps k + 2 .. k +
-  // 4 and the weight group sent at this group's start (nw loads; W4's groups are two steps, and the one sent
-  // at the start of the group before is in use by now) stay in flight.
-#define QIFT_GROUP4(k, w, nw)                                                          \
-  step(k, lds0, lds1, w[0], std::integral_constant<int, 3 * NA + nw>());               \
-  step(k + 1, lds1, lds2, w[1], std::integral_constant<int, 3 * NA + nw>());           \
-  step(k + 2, lds2, lds3, w[2], std::integral_constant<int, 3 * NA + nw>());           \
-  step(k + 3, lds3, lds0, w[3], std::integral_constant<int, 3 * NA>());
-#define QIFT_GROUP2(k, b0, b1, b2, w, nw)                                              \
-  step(k, b0, b1, w[0], std::integral_constant<int, 3 * NA + nw>());                   \
-  step(k + 1, b1, b2, w[1], std::integral_constant<int, 3 * NA + nw>());
+  // 4 and the weight group sent at this group's start stay in flight (qift_waits.h; W4's groups are two
+  // steps, and the one sent at the start of the group before is in use by now).
+#define QIFT_OUT(q, more) std::integral_constant<int, waits::batch_step(NA, NW, LS, q, more)>()
+#define QIFT_GROUP4(k, w, more)                      \
+  step(k, lds0, lds1, w[0], QIFT_OUT(0, more));      \
+  step(k + 1, lds1, lds2, w[1], QIFT_OUT(1, more));  \
+  step(k + 2, lds2, lds3, w[2], QIFT_OUT(2, more));  \
+  step(k + 3, lds3, lds0, w[3], QIFT_OUT(3, more));
+#define QIFT_GROUP2(k, b0, b1, b2, w, more)          \
+  step(k, b0, b1, w[0], QIFT_OUT(0, more));          \
+  step(k + 1, b1, b2, w[1], QIFT_OUT(1, more));
   if (GT > 0) {
     uint4 wa[LS][RJ][NB], wb[LS][RJ][NB];
     load_w(wa, 0);
@@ -207,41 +209,42 @@ __global__ __launch_bounds__(64 * NWV, NWV / 4) void k_batch(const uint32_t* __r
     issue_a(1, lds1);
     issue_a(2, lds2);
     issue_a(3, lds3);
-    __builtin_amdgcn_s_waitcnt(0x0F70 | ((3 * NA) & 15) | (((3 * NA) >> 4) << 14));
+    __builtin_amdgcn_s_waitcnt(waits::encode(waits::batch_prologue(NA), false));
     __builtin_amdgcn_sched_barrier(0);
     read_b(b, lds0);
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (LS == 4) {
-      QIFT_GROUP4(0, wa, 0)
+      QIFT_GROUP4(0, wa, false)
     } else {
-      QIFT_GROUP2(0, lds0, lds1, lds2, wa, 0)
+      QIFT_GROUP2(0, lds0, lds1, lds2, wa, false)
     }
     int g = 1;
     for (; g + 1 < GT; g += 2) {
       load_w(wa, g + 1);
       if constexpr (LS == 4) {
-        QIFT_GROUP4(4 * g, wb, NW)
+        QIFT_GROUP4(4 * g, wb, true)
         load_w(wb, g + 2);
-        QIFT_GROUP4(4 * g + 4, wa, NW)
+        QIFT_GROUP4(4 * g + 4, wa, true)
       } else {
-        QIFT_GROUP2(2 * g, lds2, lds3, lds0, wb, NW)
+        QIFT_GROUP2(2 * g, lds2, lds3, lds0, wb, true)
         load_w(wb, g + 2);
-        QIFT_GROUP2(2 * g + 2, lds0, lds1, lds2, wa, NW)
+        QIFT_GROUP2(2 * g + 2, lds0, lds1, lds2, wa, true)
       }
     }
     // a last group with no weights to load after it (loads that no MFMA uses would be dropped by the
     // compiler, and must not be counted in flight)
     if (g < GT) {
       if constexpr (LS == 4) {
-        QIFT_GROUP4(4 * g, wb, 0)
+        QIFT_GROUP4(4 * g, wb, false)
       } else {
-        QIFT_GROUP2(2 * g, lds2, lds3, lds0, wb, 0)
+        QIFT_GROUP2(2 * g, lds2, lds3, lds0, wb, false)
       }
     }
   }
 #undef QIFT_GROUP4
 #undef QIFT_GROUP2
+#undef QIFT_OUT
 
   // ---- the slices meet in LDS: tile (j, t) of wave w in buffer j, the lane's register quads 16 bytes apart
   // by 64 lanes; wave w then adds and stores the quads p = w (mod NWV) of the RJ TC 4

@@ -2,6 +2,7 @@
 #include "qift_fwht.h"   // buffer-load helpers
 #include "qift_internal.h"
 #include "qift_mma.h"
+#include "qift_waits.h"
 
 #include <type_traits>
 
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
       }
       __builtin_amdgcn_sched_barrier(0);
       if (i == NP - 3) {
-        __builtin_amdgcn_s_waitcnt(0x0070 | (OUT & 15) | ((OUT >> 4) << 14));   // vmcnt(OUT) lgkmcnt(0)
+        __builtin_amdgcn_s_waitcnt(waits::encode(OUT, true));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
   }
   s_sw[tid] = sw_pre;
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0070 | ((3 * NA) & 15) | (((3 * NA) >> 4) << 14));
+  __builtin_amdgcn_s_waitcnt(waits::encode(waits::gemm32_prologue(NA, LS), true));
   __builtin_amdgcn_s_barrier();
 #pragma unroll
   for (int i = 0; i < 3; ++i) bq[i] = read_b(lds0, i);
@@ -235,15 +236,16 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
     for (int r = 0; r < 4; ++r) a[j][r] = decode_part<FMT>(wa[0][j], 0, r);
   // A line group of W2 is four steps, of W4 two (whose buffers rotate over two groups).  The handover of
   // step k waits for the activations of step k + 1, sent three steps earlier: those of steps k + 2 and
-  // k + 3 (2 NA) and the weight loads issued since (NW a group, nw of the group before) stay in flight.
-#define QIFT_GROUP4(k, w, wn, nw)                                                              \
-  step(lds0, lds0, lds1, w[0], w[1], k, std::integral_constant<int, 2 * NA + nw>());           \
-  step(lds1, lds1, lds2, w[1], w[2], k + 1, std::integral_constant<int, 2 * NA + nw>());       \
-  step(lds2, lds2, lds3, w[2], w[3], k + 2, std::integral_constant<int, 2 * NA + nw>());       \
-  step(lds3, lds3, lds0, w[3], wn[0], k + 3, std::integral_constant<int, 2 * NA>());
-#define QIFT_GROUP2(k, b0, b1, b2, w, wn, nw)                                                  \
-  step(b0, b0, b1, w[0], w[1], k, std::integral_constant<int, 2 * NA + 2 * nw>());             \
-  step(b1, b1, b2, w[1], wn[0], k + 1, std::integral_constant<int, 2 * NA + nw>());
+  // k + 3 and the weight loads sent since stay in flight (qift_waits.h).
+#define QIFT_OUT(q, more) std::integral_constant<int, waits::gemm32_handover(NA, NW, LS, q, more)>()
+#define QIFT_GROUP4(k, w, wn, more)                                    \
+  step(lds0, lds0, lds1, w[0], w[1], k, QIFT_OUT(0, more));            \
+  step(lds1, lds1, lds2, w[1], w[2], k + 1, QIFT_OUT(1, more));        \
+  step(lds2, lds2, lds3, w[2], w[3], k + 2, QIFT_OUT(2, more));        \
+  step(lds3, lds3, lds0, w[3], wn[0], k + 3, QIFT_OUT(3, more));
+#define QIFT_GROUP2(k, b0, b1, b2, w, wn, more)                        \
+  step(b0, b0, b1, w[0], w[1], k, QIFT_OUT(0, more));                  \
+  step(b1, b1, b2, w[1], wn[0], k + 1, QIFT_OUT(1, more));
   auto load_w_here = [&](uint4 (&w)[LS][2][NB], int kt) {
     load_w(w, kt);
     __builtin_amdgcn_sched_barrier(0);
@@ -252,26 +254,27 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
   for (; kt + LS < KT; kt += 2 * LS) {
     load_w_here(wb, kt + LS);
     if constexpr (LS == 4) {
-      QIFT_GROUP4(kt, wa, wb, NW)
+      QIFT_GROUP4(kt, wa, wb, true)
       load_w_here(wa, kt + 2 * LS);
-      QIFT_GROUP4(kt + 4, wb, wa, NW)
+      QIFT_GROUP4(kt + 4, wb, wa, true)
     } else {
-      QIFT_GROUP2(kt, lds0, lds1, lds2, wa, wb, NW)
+      QIFT_GROUP2(kt, lds0, lds1, lds2, wa, wb, true)
       load_w_here(wa, kt + 2 * LS);
-      QIFT_GROUP2(kt + 2, lds2, lds3, lds0, wb, wa, NW)
+      QIFT_GROUP2(kt + 2, lds2, lds3, lds0, wb, wa, true)
     }
   }
   // an odd last group, with no weights to load after it (a load of weights that no MFMA uses would be
   // dropped by the compiler, and must not be counted in flight)
   if (kt < KT) {
     if constexpr (LS == 4) {
-      QIFT_GROUP4(kt, wa, wa, 0)
+      QIFT_GROUP4(kt, wa, wa, false)
     } else {
-      QIFT_GROUP2(kt, lds0, lds1, lds2, wa, wa, 0)
+      QIFT_GROUP2(kt, lds0, lds1, lds2, wa, wa, false)
     }
   }
 #undef QIFT_GROUP4
 #undef QIFT_GROUP2
+#undef QIFT_OUT
   __builtin_amdgcn_s_waitcnt(0x0F70);   // the loads past K have landed before a buffer is reused
   __syncthreads();
 

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qift_route.h"
+
 namespace qift {
 
 // Packing (qift_pack.hip)
@@ -62,7 +64,6 @@ hipError_t launch_gemm32(int fmt, const uint32_t* P, const uint16_t* sw, int64_t
                          const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s);
 
 // Linear on codes for batches of up to 64 tokens, K cut into a slice per wave (qift_batch.hip).
-constexpr int64_t kBatchMaxM = 64;
 hipError_t launch_batch(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                         const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s);
 
@@ -152,22 +153,18 @@ QIFT_CHAIN_LAUNCHER(launch_chain_w4);
 
 // Limits of the fused entry point.
 constexpr int64_t kFusedMaxM = 4;
-constexpr int64_t kCodesMaxM = 16;   // one MFMA column block of tokens
 // Skinny decode linear (qift_skinny.hip): up to 64 tokens in one pass over the weights, codes read
 // from memory by the K-slice waves.
-constexpr int64_t kSkinnyMaxM = 64;
-constexpr int64_t kSkinnyMaxK = 16384;
 hipError_t launch_skinny(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,
                          const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
                          uint16_t* out, int32_t* acc_out, hipStream_t s);
 // The same split over K for W2 weights (MNZ, PoT) whose few 16-row tiles would leave every workgroup
-// reading all M x K codes for 16 or 32 rows (M <= 64; up to 16 tokens only where the decode kernel on
-// codes does not fit): ws holds skinny_workspace(fmt, N, K, M) bytes (0: no split for this linear;
-// then, or with ws null, the call above).
+// reading all M x K codes for 16 or 32 rows: ws holds skinny_workspace(fmt, N, K, M) bytes (0: no split
+// for this linear, which the call then refuses).
 size_t skinny_workspace(int fmt, int64_t N, int64_t K, int64_t M);
-hipError_t launch_skinny_ws(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,
-                            const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
-                            uint16_t* out, int32_t* acc_out, void* ws, hipStream_t s);
+hipError_t launch_skinny_split(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,
+                               const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
+                               uint16_t* out, int32_t* acc_out, void* ws, hipStream_t s);
 constexpr int64_t kFusedMaxK = 16384;
 constexpr int kFusedMaxBlock = 4096;
 // Largest K accepted by the activation quantizer.

@@ -4,6 +4,7 @@
 #include "qift_fwht.h"   // buffer-load helpers
 #include "qift_internal.h"
 #include "qift_mma.h"
+#include "qift_route.h"
 #include "qift_split.h"
 
 namespace qift {
@@ -525,93 +526,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_split(const uint32_t* __restric
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// Above 64 tokens with a workspace, where the 256 x 64 tiles are few (down at 65-512 tokens: 16 x
-// ceil(M / 64) tiles, each a chain of 56 W2 or 112 W4 steps whose loads are not hidden), the GEMM may be
-// split over K at two workgroups per CU: S ranges of at least 4 W2 or 8 W4 steps (1024 k), about 512
-// workgroups and no more than are resident at once.  At 65 / 128 / 1024 tokens, W2 (the unsplit GEMM):
-// down 20 / 24 / 62 us (49 / 49 / 75).  W4 takes at least three ranges (two measured no faster).  From 33
-// tokens on (W4 24) wide (N >= 16384) and long (N >= 4096, K > 4096) linears have a plan too.  The plan
-// sizes the workspace; take_split says where it is the faster.
-constexpr int64_t kSplitTarget = 512, kSplitResident = 512, kSplitWideMinM = 33, kSplitWideMinMW4 = 24,
-                  kSplitWideMinN = 16384,
-                  kSplitLongMinN = 4096, kSplitLongMinK = 4097;
-struct GemmSplit {
-  int S = 1, us = 0;
-};
-inline GemmSplit gemm_split_plan(int fmt, int64_t N, int64_t M, int64_t K) {
-  GemmSplit p;
-  const int64_t bk = fmt == FMT_W4 ? 128 : 256, min_steps = fmt == FMT_W4 ? 8 : 4, min_s = fmt == FMT_W4 ? 3 : 2;
-  const int64_t tiles = ((N + 255) / 256) * ((M + 63) / 64), KT = (K + bk - 1) / bk;
-  p.us = (int)KT;
-  const bool wide = M >= (fmt == FMT_W4 ? kSplitWideMinMW4 : kSplitWideMinM) &&
-                    (N >= kSplitWideMinN || (N >= kSplitLongMinN && K >= kSplitLongMinK));
-  if (M <= kSkinnyMaxM && !wide) return p;
-  int64_t S = (kSplitTarget + tiles - 1) / tiles;
-  if (S > kSplitResident / tiles) S = kSplitResident / tiles;
-  if (S > KT / min_steps) S = KT / min_steps;
-  if (S < min_s) return p;
-  p.us = (int)((KT + S - 1) / S);
-  p.S = (int)((KT + p.us - 1) / p.us);
-  return p;
-}
-
-// Whether the split plan is also the faster choice.  A short K (below 8192) has few steps to share out
-// and pays the second pass (4-5 us) and the partial sums: it splits only while the tiles are few, W2 up
-// to 64 of them (4096 x 4096, split against not, us: 12.4 / 16.5 at 100 tokens, 14.5 / 16.5 at 256, but
-// 19 / 16.6 at 300 and 27 / 17.8 at 600; 12288 x 4096 19.9 / 17.5 at 100), W4 up to 96 (6144 x 4096 21.5 /
-// 22.3 at 192, 24 / 22.3 at 300).  Wide linears of a short K do not split where the GEMM takes them
-// (gemm_wide); up to 64 tokens most linears go to the batch kernel first (take_batch).  A long K splits
-// wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at 1024).
-inline bool gemm_wide(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
-  // From 33 tokens on a wide linear that the batch kernel leaves (take_batch) runs the tiled GEMM rather than
-  // the skinny kernel, whose workgroups each read all M x K codes (28672 x 4096 at 33 / 64 tokens: W2 22.9 ->
-  // 17.3 / 28.2 -> 18.6 us), and unsplit unless K is long.
-  if (N < kSplitWideMinN || M < kSplitWideMinM) return false;
-  return !ws || K < 8192;
-}
-// The batch kernel (K cut into a slice per wave), up to 64 tokens.  Its time hardly grows with the tokens,
-// so it is the faster from some count on; where, by what it replaces (us at 4096-k unless said, old / batch):
-//   17-64 tokens, the skinny kernel (workgroups that read all codes), its split and the split GEMM:
-//     wide (N >= 16384): W2 16.6 / 14.4 at 17, 22016 rows 17.8 / 12.2 at 32 and 18.2 / 16.3 at 64, W4 21.4 /
-//     16.2 at 24; not W2 of more than 24576 rows from 33 tokens on, the tiled GEMM's (28672: 18.6 / 20.2);
-//     others: 12288 rows 8.7 / 8.3 at 17, W4 23.4 / 12.5 at 64; 4096 rows 6.5 / 6.3 at 24 (5.9 / 6.2 at 17) and
-//     10.8 / 6.6 at 64; a short K (2048) from 48 tokens, W4 6.0 / 5.7 (4.8 / 5.2 at 32).  W4 of a long K with a
-//     workspace stays with the split GEMM below 33 tokens (4096 x 11008 12.4 / 12.9 at 24);
-//   5-16 tokens, the decode kernel on codes: wide and K > 4096 (16384 x 8192, whose one 16-row tile per
-//     workgroup takes four rounds: 23.4 / 13.4 at 9, W4 29.3 / 20.6 at 12); W2 of at most 16384 rows from 12
-//     tokens (at 16: 6144 rows 7.3 / 5.7, 4096 6.4 / 5.5, 12288 8.3 / 7.9, 4096 x 11008 9.3 / 8.6), 4097-8192
-//     rows from 9 (6.1 / 5.6 at 8); W4 from 15 tokens, wide or at most 4096 rows (28672 22.2 / 20.1, 4096 x
-//     11008 13.6 / 11.2, 4096 6.5 / 6.3 at 16, but 12288 9.0 / 9.3); and from 9 where the codes exceed its LDS
-//     (4096 x 14336 at 16: 14.5 / 10.2, with a workspace 10.3 / 10.2; K = 20480 15.0 / 13.6 at 9);
-//   K > 16384 from 17 tokens on, the prefill GEMM (4096 x 20480 at 24: 70 / 14.7).
-inline bool take_batch(int fmt, int64_t N, int64_t M, int64_t K, bool ws) {
-  const bool w4 = fmt == FMT_W4;
-  if (M > kBatchMaxM || M < 5) return false;
-  if (M > kCodesMaxM) {
-    if (K > kSkinnyMaxK) return true;
-    if (N >= kSplitWideMinN) return K >= 2048 && (w4 || M <= 32 || N <= 24576);
-    if (M >= 48) return K >= 2048;
-    if (K < 4096) return false;
-    if (N > 4096) return true;
-    if (w4) return K > 8192 ? !ws || M < kSplitWideMinMW4 || M >= 33 : M >= 24;
-    return M >= 24 || N <= 2048;
-  }
-  if (N >= kSplitWideMinN && K > 4096) return !w4 || M >= 9;
-  if (K >= 4096 && M >= 15 && w4 && (N >= kSplitWideMinN || N <= 4096)) return true;
-  if (K >= 4096 && !w4 && N <= kSplitWideMinN && M >= (N > 4096 && N <= 8192 ? 9 : 12)) return true;
-  const size_t cs = fmt == FMT_MNZ ? codes_shmem_mnz(M, N, K) : fmt == FMT_POT ? codes_shmem_pot(M, N, K)
-                                                                               : codes_shmem_w4(M, N, K);
-  return (cs == 0 || cs > 160 * 1024) && M >= (w4 ? 12 : 9) && !(ws && skinny_workspace(fmt, N, K, M) != 0);
-}
-inline bool take_split(const GemmSplit& p, int fmt, int64_t N, int64_t M, int64_t K) {
-  if (p.S < 2) return false;
-  if (K >= 8192 || M <= kSkinnyMaxM) return !gemm_wide(fmt, N, M, K, true);
-  const int64_t tiles = ((N + 255) / 256) * ((M + 63) / 64);
-  return tiles <= (fmt == FMT_W4 ? 96 : 64) && !gemm_wide(fmt, N, M, K, true);
-}
-
 template <int FMT, bool SUMQ>
-hipError_t launch_gemm_split(const GemmSplit& p, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
+hipError_t launch_gemm_split(const route::GemmSplit& p, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
                            const int8_t* act, const float* sx, const int32_t* asum, int64_t M, uint16_t* y,
                            int32_t* acc_out, void* ws, hipStream_t s) {
   int32_t* part = static_cast<int32_t*>(ws);
@@ -683,49 +599,41 @@ hipError_t launch_deep(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t
 #undef QIFT_DEEP
 }
 
+inline bool codes_fit(int fmt, int64_t M, int64_t N, int64_t K) {
+  const size_t cs = fmt == FMT_MNZ ? codes_shmem_mnz(M, N, K) : fmt == FMT_POT ? codes_shmem_pot(M, N, K)
+                                                                               : codes_shmem_w4(M, N, K);
+  return cs != 0 && cs <= 160 * 1024;
+}
+
 template <int FMT>
 hipError_t launch_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                       const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
                       hipStream_t s) {
-  if (take_batch(FMT, N, M, K, ws != nullptr)) return launch_batch(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
-  if (ws) {
-    const GemmSplit p = gemm_split_plan(FMT, N, M, K);
-    if (take_split(p, FMT, N, M, K))
+  constexpr bool w4 = FMT == FMT_W4;
+  switch (route::choose(w4, N, K, M, codes_fit(FMT, M, N, K), ws != nullptr)) {
+    case route::kBatch: return launch_batch(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    case route::kGemmSplit: {
+      const route::GemmSplit p = route::gemm_split_plan(w4, N, M, K);
       return asum ? launch_gemm_split<FMT, false>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s)
                   : launch_gemm_split<FMT, true>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
-  }
-  if (gemm_wide(FMT, N, M, K, ws != nullptr))
-    return launch_gemm32(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
-  // 17..64 tokens: the skinny kernel, one pass over the weights (the codes of that many tokens do not
-  // fit the decode kernel's LDS, and the GEMM's grid of N/256 workgroups would leave most CUs idle)
-  if (M > kCodesMaxM && M <= kSkinnyMaxM && K <= kSkinnyMaxK)
-    return launch_skinny_ws(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
-  if (M <= kCodesMaxM) {
-    // the decode kernel on precomputed codes (K-slice weight waves, the codes staged in LDS)
-    const size_t cs = FMT == FMT_MNZ ? codes_shmem_mnz(M, N, K) : FMT == FMT_POT ? codes_shmem_pot(M, N, K)
-                                                                                  : codes_shmem_w4(M, N, K);
-    if (cs != 0 && cs <= 160 * 1024) {
+    }
+    case route::kGemm: return launch_gemm32(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    case route::kSkinny: return launch_skinny(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    case route::kSkinnySplit: return launch_skinny_split(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
+    case route::kCodes:
       if constexpr (FMT == FMT_MNZ) return launch_codes_mnz(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
       else if constexpr (FMT == FMT_POT) return launch_codes_pot(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
       else return launch_codes_w4(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
-    }
-    // codes beyond LDS (e.g. 16 tokens of K = 14336): with a workspace the skinny linear split over K;
-    // else the decode kernels that read them from memory (measured faster there than the skinny
-    // kernel unsplit with one token tile: 16 tokens at K = 14336)
-    if constexpr (FMT != FMT_W4) {
-      if (ws && skinny_workspace(FMT, N, K, M) != 0)
-        return launch_skinny_ws(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
-    }
-    if (M * kpad_of(K) <= kDecodeMaxLds) return launch_deep<FMT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
-    return launch_decode<FMT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    case route::kDecode: break;
   }
-  return launch_gemm32(FMT, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+  if (M * kpad_of(K) <= kDecodeMaxLds) return launch_deep<FMT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+  return launch_decode<FMT>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
 }
 
 }  // namespace
 
 size_t gemm_split_workspace(int fmt, int64_t N, int64_t M, int64_t K) {
-  const GemmSplit p = gemm_split_plan(fmt, N, M, K);
+  const route::GemmSplit p = route::gemm_split_plan(fmt == FMT_W4, N, M, K);
   return p.S > 1 ? split::part_bytes(p.S, M, N) + (size_t)p.S * (size_t)M * 4 : 0;
 }
 

@@ -21,8 +21,7 @@
 // tokens), so a linear with K > 4096 and few 16-row tiles (down) takes four tiles per workgroup and
 // gives each workgroup a range of K instead: workgroup (x, z) writes its int32 partial sums of tile
 // group x over unit range z to the workspace, and the second pass (qift_split.h) adds the ranges (integers: exact in any
-// order) and applies the epilogue (down at 17 tokens: 11.7 -> 10.3 us; from 24 tokens on the batch kernel
-// takes such linears).
+// order) and applies the epilogue (1000 x 14336 at 17 tokens 12.1 -> 8.8 us; which linears: qift_route.h).
 #include "qift_fwht.h"
 #include "qift_internal.h"
 #include "qift_mma.h"
@@ -33,7 +32,6 @@ namespace {
 
 using namespace mma;
 
-constexpr int kSkSlices = 8;
 
 // VGPRs of a lane's accumulators (MNZ by bit plane below four token tiles: two per tile pair), weight
 // groups (U units of T tiles) and one unit's codes
@@ -268,35 +266,7 @@ hipError_t launch_skinny_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, i
 
 // ---- split over K (W2 formats, with a workspace)
 
-// The split of a linear: T = 4 tiles per workgroup, S ranges of us units each, chosen for about one
-// workgroup per CU with at most two units per slice; S = 0 for K <= 4096 (the codes per workgroup are
-// few enough: measured faster unsplit) and when a linear has tiles enough without a split (gate|up).
-// Also for up to 16 tokens whose codes the decode kernel cannot stage in LDS (it would read them from
-// memory per 16-row tile instead).
-struct SkSplit {
-  int T = 0, S = 0, us = 0, np = 0;
-};
-
-inline SkSplit split_plan(int fmt, int64_t N, int64_t K, int64_t M) {
-  SkSplit p;
-  if (fmt == FMT_W4 || M < 1 || M > kSkinnyMaxM || K > kSkinnyMaxK || N < 1 || K < 1) return p;
-  const int T = 4;
-  const int64_t tiles = (N + 15) / 16, gx = (tiles + T - 1) / T;
-  const int ut = (int)((K + 255) / 256);
-  if (ut <= 16) return p;
-  int S = (int)((256 + gx / 2) / gx);
-  if (S < 2) return p;
-  const int min_s = (ut + kSkSlices * 2 - 1) / (kSkSlices * 2);   // at most two units per slice
-  if (S < min_s) S = min_s;
-  if (S > ut) S = ut;
-  const int us = (ut + S - 1) / S;
-  p.T = T;
-  p.us = us;
-  p.S = (ut + us - 1) / us;   // every range holds at least one unit
-  p.np = (int)((N + 3) / 4 * 4);
-  if (p.S < 2) p.S = 0;
-  return p;
-}
+using route::SkSplit;
 
 inline size_t split_part_bytes(const SkSplit& p, int64_t M, int64_t N) { return split::part_bytes(p.S, M, N); }
 
@@ -328,7 +298,8 @@ hipError_t launch_split_fmt(const SkSplit& p, const uint32_t* P, const uint16_t*
                             const int8_t* act, const float* sx, const int32_t* asum, int64_t M, uint16_t* y,
                             int32_t* acc_out, void* ws, hipStream_t s) {
 #define QIFT_SPLIT(T_, TT_) launch_split_t<FMT, T_, TT_>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s)
-  if (M > 32) return hipErrorInvalidValue;   // the batch kernel's
+  if (p.S < 2 || M > kSkSplitMaxM) return hipErrorInvalidValue;
+  if (M > 32) return QIFT_SPLIT(4, 4);
   return M <= 16 ? QIFT_SPLIT(4, 1) : QIFT_SPLIT(4, 2);
 #undef QIFT_SPLIT
 }
@@ -340,20 +311,19 @@ size_t skinny_workspace(int fmt, int64_t N, int64_t K, int64_t M) {
     const size_t cs = fmt == FMT_MNZ ? codes_shmem_mnz(M, N, K) : fmt == FMT_POT ? codes_shmem_pot(M, N, K) : 0;
     if (cs != 0 && cs <= 160 * 1024) return 0;
   }
-  const SkSplit p = split_plan(fmt, N, K, M);
+  const SkSplit p = route::skinny_split_plan(fmt == FMT_W4, N, M, K);
   if (p.S == 0) return 0;
   return split_part_bytes(p, M, N) + (size_t)p.S * (size_t)M * 4;
 }
 
-hipError_t launch_skinny_ws(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
-                            const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
-                            hipStream_t s) {
-  const SkSplit p = split_plan(fmt, N, K, M);
-  if (ws == nullptr || p.S == 0 || M > 32) return launch_skinny(fmt, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+hipError_t launch_skinny_split(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
+                               const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
+                               hipStream_t s) {
+  const SkSplit p = route::skinny_split_plan(fmt == FMT_W4, N, M, K);
   switch (fmt) {
     case FMT_MNZ: return launch_split_fmt<FMT_MNZ>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
     case FMT_POT: return launch_split_fmt<FMT_POT>(p, P, sw, N, K, act, sx, asum, M, y, acc_out, ws, s);
-    default: return launch_skinny(fmt, P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

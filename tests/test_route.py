@@ -1,0 +1,122 @@
+"""Which kernel a linear on codes runs (csrc/qift_route.h), on the CPU.
+
+The rule is compiled here from the header that the library uses and asked about sizes whose kernels were timed.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_02823_amd", "csrc")
+KERNELS = ["batch", "gemm_split", "gemm", "skinny", "skinny_split", "codes", "decode"]
+PROBE = """
+#include <cstdio>
+#include "qift_route.h"
+using namespace qift;
+int main() {
+  long w4, N, K, M, codes, ws;
+  while (std::scanf("%ld %ld %ld %ld %ld %ld", &w4, &N, &K, &M, &codes, &ws) == 6)
+    std::printf("%d %d %d\\n", (int)route::choose(w4, N, K, M, codes, ws), route::gemm_split_plan(w4, N, M, K).S,
+                route::skinny_split_plan(w4, N, M, K).S);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """list of (w4, N, K, M, codes fit LDS, workspace) -> list of (kernel, GEMM ranges, skinny ranges)."""
+    cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
+    d = tmp_path_factory.mktemp("route")
+    (d / "probe.cpp").write_text(PROBE)
+    subprocess.run([cxx, "-std=c++17", "-I", CSRC, str(d / "probe.cpp"), "-o", str(d / "probe")], check=True)
+
+    def run(queries):
+        out = subprocess.run([str(d / "probe")], input="".join("%d %d %d %d %d %d\n" % tuple(q) for q in queries),
+                             text=True, capture_output=True, check=True).stdout.splitlines()
+        assert len(out) == len(queries)
+        rows = [[int(v) for v in line.split()] for line in out]
+        return [(KERNELS[k], s, t) for k, s, t in rows]
+
+    return run
+
+
+# (W4, N, K, M, workspace, us of the kernels that take it): sizes on both sides of each line of the rule
+MEASURED = [
+    # more rows than one round of batch workgroups
+    (0, 40960, 4096, 33, 0, {"batch": 34.89, "gemm": 20.28, "skinny": 33.77}),
+    (0, 40960, 20480, 33, 1, {"batch": 125.15, "gemm_split": 66.53, "gemm": 86.06}),
+    (1, 40960, 4096, 48, 0, {"batch": 43.26, "gemm": 28.46, "skinny": 52.72}),
+    (1, 40960, 2048, 17, 0, {"batch": 22.32, "skinny": 14.56}),
+    # wide, short K
+    (0, 16384, 2048, 17, 0, {"batch": 8.38, "skinny": 5.94}),
+    (0, 28672, 2048, 24, 0, {"batch": 10.25, "skinny": 9.08}),
+    (1, 28672, 2048, 20, 0, {"batch": 13.11, "skinny": 10.66}),
+    (0, 16384, 1024, 48, 0, {"batch": 7.84, "gemm": 8.32, "skinny": 7.24}),
+    (1, 16384, 1024, 33, 0, {"batch": 7.47, "gemm": 9.62, "skinny": 7.47}),
+    # long K with the skinny split
+    (0, 1000, 14336, 17, 1, {"batch": 11.12, "skinny": 12.23, "skinny_split": 8.92}),
+    (0, 1000, 14336, 32, 1, {"batch": 11.54, "skinny": 16.67, "skinny_split": 9.60}),
+    (0, 2048, 14336, 16, 1, {"batch": 9.67, "skinny_split": 8.30, "decode": 13.67}),
+    (0, 2048, 11008, 20, 1, {"batch": 9.32, "skinny": 11.52, "skinny_split": 8.73}),
+    (0, 4096, 14336, 24, 1, {"batch": 14.11, "skinny": 15.56, "skinny_split": 12.41}),
+    (0, 1000, 14336, 33, 1, {"batch": 11.27, "skinny_split": 10.21}),
+    (0, 300, 16384, 40, 1, {"batch": 11.61, "skinny_split": 10.44}),
+    (0, 4096, 11008, 16, 1, {"batch": 8.36, "skinny_split": 9.36, "decode": 11.47}),
+    # just past 4096 k, few rows
+    (0, 300, 5120, 12, 0, {"batch": 6.08, "codes": 5.58}),
+    (0, 1000, 5120, 17, 0, {"batch": 7.72, "skinny": 6.62}),
+    (1, 300, 4096, 15, 0, {"batch": 5.74, "codes": 5.05}),
+    (1, 4096, 5120, 15, 0, {"batch": 7.66, "codes": 7.19}),
+    # W4, long K, 17 to 27 tokens
+    (1, 3072, 11008, 20, 0, {"batch": 15.13, "skinny": 13.52}),
+    (1, 4096, 11008, 17, 0, {"batch": 15.22, "skinny": 13.45}),
+    # very long K with the split GEMM
+    (1, 4096, 16384, 33, 1, {"batch": 18.50, "gemm_split": 16.98, "skinny": 26.32}),
+    (1, 12288, 20480, 40, 1, {"batch": 49.87, "gemm_split": 42.38, "gemm": 115.40}),
+    (0, 12288, 20480, 33, 1, {"batch": 35.24, "gemm_split": 30.55, "gemm": 82.17}),
+    (0, 28672, 20480, 48, 1, {"batch": 67.40, "gemm_split": 56.18, "gemm": 84.44}),
+    (0, 22016, 11008, 33, 1, {"batch": 34.29, "gemm_split": 31.76, "gemm": 46.42}),
+    (1, 28672, 14336, 33, 1, {"batch": 64.34, "gemm_split": 57.68, "gemm": 77.25}),
+    # what the batch kernel and the GEMM keep
+    (0, 4096, 4096, 24, 0, {"batch": 6.27, "skinny": 6.59}),
+    (0, 6144, 4096, 9, 0, {"batch": 5.63, "codes": 6.59}),
+    (1, 12288, 4096, 48, 0, {"batch": 13.26, "gemm": 25.14, "skinny": 22.02}),
+    (0, 22016, 4096, 64, 1, {"batch": 16.58, "gemm_split": 23.65, "gemm": 19.31, "skinny": 28.12}),
+    (0, 28672, 4096, 64, 1, {"batch": 20.22, "gemm_split": 25.55, "gemm": 19.88, "skinny": 28.72}),
+    (1, 22016, 4096, 40, 1, {"batch": 19.79, "gemm_split": 24.46, "gemm": 25.54, "skinny": 30.20}),
+    (0, 4096, 14336, 64, 1, {"batch": 14.47, "gemm_split": 16.48, "gemm": 52.63, "skinny": 30.35}),
+    (1, 28672, 4096, 16, 0, {"batch": 20.33, "codes": 22.99}),
+    (0, 16384, 8192, 9, 0, {"batch": 13.41, "codes": 24.05}),
+]
+
+
+@pytest.mark.parametrize("w4,N,K,M,ws,us", MEASURED, ids=[f"{'w4' if c[0] else 'w2'}-{c[1]}x{c[2]}-m{c[3]}" for c in MEASURED])
+def test_route_takes_the_faster_kernel(ask, w4, N, K, M, ws, us):
+    kernel, _, _ = ask([(w4, N, K, M, "codes" in us, ws)])[0]
+    # 4 %: twice what repeated timings of one kernel differed by
+    assert us[kernel] <= 1.04 * min(us.values()), (kernel, us)
+
+
+def test_route_stays_within_the_kernels_limits(ask):
+    Ns = [1, 16, 63, 300, 1000, 2048, 4095, 4096, 4097, 8192, 8193, 12288, 16383, 16384, 16385, 24576, 24577, 32768, 32769, 70000]
+    Ks = [64, 256, 1088, 2048, 3072, 4096, 4160, 8192, 8256, 11008, 12288, 14336, 16384, 16448, 20480, 65536]
+    Ms = [1, 4, 5, 8, 9, 12, 16, 17, 24, 28, 32, 33, 48, 64, 65, 200, 2048]
+    qs = [(w4, N, K, M, c, ws) for w4 in (0, 1) for N in Ns for K in Ks for M in Ms
+          for c in ((0, 1) if M <= 16 and K <= 16384 else (0,)) for ws in (0, 1)]
+    for (w4, N, K, M, codes, ws), (kernel, gemm_ranges, skinny_ranges) in zip(qs, ask(qs)):
+        q = (w4, N, K, M, codes, ws, kernel)
+        if kernel == "batch":
+            assert 5 <= M <= 64, q
+        elif kernel == "gemm_split":
+            assert ws and gemm_ranges >= 2, q
+        elif kernel == "gemm":
+            assert M > 16, q
+        elif kernel == "skinny":
+            assert 16 < M <= 64 and K <= 16384, q
+        elif kernel == "skinny_split":
+            assert ws and not w4 and M <= 47 and K <= 16384 and skinny_ranges >= 2 and not (M <= 16 and codes), q
+        elif kernel == "codes":
+            assert codes and M <= 16, q
+        else:
+            assert M <= 16 and not codes, q

@@ -292,9 +292,9 @@ int qift_rotate_quant_act_bf16(const uint16_t *x, int64_t M, qift_hadamard_spec 
  *   act_q, act_scale   the codes and scales of qift_rotate_quant_act for M
  *              tokens of width w->K (codes in -7..7).
  *   out        out: fp16 y [M][N].
- * The kernels run the MFMA on the raw 2-bit codes and add the exact level
- * correction from the per-token sum of the codes, which they compute from
- * the act_q tiles they stage.  Up to 16 tokens the decode kernel on codes, up
+ * The kernels up to 64 tokens run the MFMA on the raw 2-bit codes and add the
+ * exact level correction from the per-token sum of the codes, which they
+ * compute from the act_q tiles they stage; the prefill GEMM runs on the levels.  Up to 16 tokens the decode kernel on codes, up
  * to 64 the batch kernel (from 9 to 15 tokens on for most weights) or the
  * skinny one, beyond the tiled prefill GEMM; all give identical results.
  */

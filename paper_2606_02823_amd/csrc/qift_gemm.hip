@@ -23,18 +23,36 @@ constexpr int wload16() { return FMT == FMT_W4 ? 2 : 1; }   // 16-byte loads per
 template <int FMT>
 constexpr int line_steps() { return FMT == FMT_W4 ? 2 : 4; }   // steps in 128 bytes of a weight row
 
-// register r of the MFMA operand s of a lane's weights of one step (decode_unit, one register)
-template <int FMT>
+// What the weight operands of the MFMA hold.
+//   kCodes    the raw codes: the exact correction needs the per-token code sums, which the caller gives (MNZ, W4)
+//   kLevels   the levels, W4's times 16: no sums (PoT, and the others where none are given)
+//   kLevels1  the levels of W4 as they are, where 16 times the accumulator may not fit int32 (K > 2^21)
+enum Operand { kCodes, kLevels, kLevels1 };
+
+// register r of the MFMA operand s of a lane's weights of one step
+template <int FMT, int OP>
 __device__ __forceinline__ int decode_part(const uint4 (&u)[FMT == FMT_W4 ? 2 : 1], int s, int r) {
   if constexpr (FMT == FMT_W4) {
     const uint4 h = u[s >> 1];
     const uint32_t w = (s & 1) ? (r < 2 ? h.z : h.w) : (r < 2 ? h.x : h.y);
-    return (int)((r & 1 ? w >> 4 : w) & 0x0F0F0F0Fu);
+    // nibble u = q + 8: in the upper half of a byte with its top bit flipped it is 16 q
+    if constexpr (OP == kLevels) return (int)(((r & 1 ? w : w << 4) & 0xF0F0F0F0u) ^ 0x80808080u);
+    const uint32_t c = (r & 1 ? w >> 4 : w) & 0x0F0F0F0Fu;
+    // u + 120 stays within the byte, and is 128 + q
+    return OP == kLevels1 ? (int)((c + 0x78787878u) ^ 0x80808080u) : (int)c;
   } else {
     const uint32_t w = s == 0 ? u[0].x : s == 1 ? u[0].y : s == 2 ? u[0].z : u[0].w;
     const uint32_t c = (w >> (2 * r)) & 0x03030303u;
-    return FMT == FMT_POT ? (int)__builtin_amdgcn_perm(0u, 0x0401FFFCu, c) : (int)c;   // {-4, -1, +1, +4}
+    if constexpr (FMT == FMT_POT) return (int)__builtin_amdgcn_perm(0u, 0x0401FFFCu, c);   // {-4, -1, +1, +4}
+    return OP == kCodes ? (int)c : (int)__builtin_amdgcn_perm(0u, 0x0301FFFDu, c);         // {-3, -1, +1, +3}
   }
+}
+
+// the accumulator from the MFMA sum D
+template <int FMT, int OP>
+__device__ __forceinline__ int finish(int D, int sum_q) {
+  if constexpr (OP == kCodes) return finish_acc<FMT>(D, sum_q);
+  else return FMT == FMT_W4 && OP == kLevels ? D >> 4 : D;
 }
 
 // slot of 16-byte column c of activation row r
@@ -60,8 +78,11 @@ __device__ __forceinline__ int slot(int r, int c) { return c ^ (((r >> 1) & 7) ^
 // At 2048 tokens, us before (256 x 64 tiles of 16-wide MFMAs, three workgroups to a CU) -> now: W2 28672 x
 // 4096 221 -> 187 (2.57 POP/s), 4096 x 4096 40 -> 33, 4096 x 14336 105 -> 94; W4 253 -> 206, 49 -> 36, 137 ->
 // 108.  At 512: W2 73 -> 56, 27.2 -> 17.3, 66.7 -> 51.
-// With SUMQ (no per-token sums given) wave t also adds up the codes of token tile t.
-template <int FMT, int TC, bool SUMQ>
+// Without per-token sums (the plain calls) the operands are the levels, so that none are needed: one byte permute a
+// register for MNZ, nothing for W4.  (Sums added up in the loop spilled 28 registers of MNZ's 128-token
+// instance, whose reloads drained the loads in flight: 4096 x 14336 at 2048 tokens 118 -> 103 us, with sums 95; 28672 x
+// 4096 at 1024 tokens 125 -> 107.)
+template <int FMT, int TC, int OP>
 __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ P, const uint16_t* __restrict__ sw,
                                                      int N, int K, const int8_t* __restrict__ act,
                                                      const float* __restrict__ sx, const int32_t* __restrict__ asum,
@@ -142,7 +163,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
     for (int t = 0; t < TC; ++t)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[j][t][i] = 0;
-  int sq = 0;
 
   int boff[4];
 #pragma unroll
@@ -178,19 +198,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int r = 4 * t / TC; r < 4 * (t + 1) / TC; ++r)
-          an[j][r] = s < 3 ? decode_part<FMT>(w[j], s + 1, r) : decode_part<FMT>(wnx[j], 0, r);
+          an[j][r] = s < 3 ? decode_part<FMT, OP>(w[j], s + 1, r) : decode_part<FMT, OP>(wnx[j], 0, r);
       if (i >= NP - 2) {
 #pragma unroll
         for (int q = 0; q < NA / 2; ++q) issue_a(kt + 4, own, q + (i - (NP - 2)) * (NA / 2));
       }
       acc[1 - j0][t] = mfma32_i8(a[1 - j0], b, acc[1 - j0][t]);
-      if constexpr (SUMQ) {   // the sums of token tile t by wave t
-        // (its last read of the step before the barrier)
-        if (i == 3 * TC - 1 || (t == 0 && s < 3)) {
-          const int sr = i == 3 * TC - 1 ? 3 : s;
-          sq = sum16_i8(*reinterpret_cast<const uint4*>(cur + 32 * kBK * (wave & (TC - 1)) + boff[sr]), sq);
-        }
-      }
       if (t == TC - 1) {
         a[0] = an[0];
         a[1] = an[1];
@@ -211,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
   // scales and sums of the tile for the epilogue (their loads go out before the tile's)
   const float sx_pre = tid < mrows ? sx[m_base + tid] : 0.f;
   int sum_pre = 0;
-  if constexpr (!SUMQ) sum_pre = tid < mrows ? asum[m_base + tid] : 0;
+  if constexpr (OP == kCodes) sum_pre = tid < mrows ? asum[m_base + tid] : 0;
   const uint16_t sw_pre = tn * 256 + tid < N ? sw[tn * 256 + tid] : (uint16_t)0;
   __builtin_amdgcn_sched_barrier(0);
   uint4 wa[LS][2][NB], wb[LS][2][NB];
@@ -222,7 +235,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
   issue_all(3, lds3);
   if (tid < BM) {
     s_sx[tid] = sx_pre;
-    if constexpr (!SUMQ) s_sum[tid] = sum_pre;
+    if constexpr (OP == kCodes) s_sum[tid] = sum_pre;
   }
   s_sw[tid] = sw_pre;
   __builtin_amdgcn_sched_barrier(0);
@@ -233,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[j][r] = decode_part<FMT>(wa[0][j], 0, r);
+    for (int r = 0; r < 4; ++r) a[j][r] = decode_part<FMT, OP>(wa[0][j], 0, r);
   // A line group of W2 is four steps, of W4 two (whose buffers rotate over two groups).  The handover of
   // step k waits for the activations of step k + 1, sent three steps earlier: those of steps k + 2 and
   // k + 3 and the weight loads sent since stay in flight (qift_waits.h).
@@ -278,17 +291,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
   __builtin_amdgcn_s_waitcnt(0x0F70);   // the loads past K have landed before a buffer is reused
   __syncthreads();
 
-  if constexpr (SUMQ) {
-    sq += __shfl_xor(sq, 32);
-    if (wave < TC && h == 0) s_sum[32 * wave + r32] = sq;
-    __syncthreads();
-  }
   float sxt[TC];
   int sqt[TC];
 #pragma unroll
   for (int t = 0; t < TC; ++t) {
     sxt[t] = s_sx[32 * t + r32];
-    sqt[t] = s_sum[32 * t + r32];
+    sqt[t] = 0;
+    if constexpr (OP == kCodes) sqt[t] = s_sum[32 * t + r32];
   }
   // D of tile (j, t): register 4 q + i of lane (token r32, half h) is row 32 j + 8 q + 4 h + i
   if (acc_out == nullptr) {
@@ -312,7 +321,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
         for (int t = 0; t < TC; ++t) {
           uint32_t o[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[i] = epilogue(finish_acc<FMT>(acc[j][t][4 * q + i], sqt[t]), sxt[t], s4[i]);
+          for (int i = 0; i < 4; ++i) o[i] = epilogue(finish<FMT, OP>(acc[j][t][4 * q + i], sqt[t]), sxt[t], s4[i]);
           const int c = 8 * wave + 4 * j + q;
           *reinterpret_cast<uint2*>(row_at(t, r32) + 16 * (c ^ r32) + 8 * h) =
               make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
@@ -352,24 +361,22 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          store4_sw<FMT>(v4i{acc[j][t][4 * q], acc[j][t][4 * q + 1], acc[j][t][4 * q + 2], acc[j][t][4 * q + 3]}, m,
-                         n_base + 32 * j + 8 * q + 4 * h, N, sxt[t], sqt[t],
-                         *reinterpret_cast<const uint2*>(s_sw + 64 * wave + 32 * j + 8 * q + 4 * h), y, acc_out);
+          // (the accumulators as they are: PoT's form of the store)
+          store4_sw<FMT_POT>(v4i{finish<FMT, OP>(acc[j][t][4 * q], sqt[t]), finish<FMT, OP>(acc[j][t][4 * q + 1], sqt[t]),
+                                 finish<FMT, OP>(acc[j][t][4 * q + 2], sqt[t]), finish<FMT, OP>(acc[j][t][4 * q + 3], sqt[t])},
+                             m, n_base + 32 * j + 8 * q + 4 * h, N, sxt[t], 0,
+                             *reinterpret_cast<const uint2*>(s_sw + 64 * wave + 32 * j + 8 * q + 4 * h), y, acc_out);
     }
   }
 }
 
-template <int FMT, int TC>
+template <int FMT, int TC, int OP>
 hipError_t launch_t(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act, const float* sx,
                     const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s) {
   const int tn = (int)((N + 255) / 256), tm = (int)((M + 32 * TC - 1) / (32 * TC));
   const dim3 grid((unsigned)tn * (unsigned)tm);
-  if (asum)
-    hipLaunchKernelGGL((k_gemm32<FMT, TC, false>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum,
-                       (int)M, tn, tm, y, acc_out);
-  else
-    hipLaunchKernelGGL((k_gemm32<FMT, TC, true>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum,
-                       (int)M, tn, tm, y, acc_out);
+  hipLaunchKernelGGL((k_gemm32<FMT, TC, OP>), grid, dim3(256), 0, s, P, sw, (int)N, (int)K, act, sx, asum, (int)M, tn, tm,
+                     y, acc_out);
   return hipGetLastError();
 }
 
@@ -389,8 +396,14 @@ hipError_t launch_f(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
   const int64_t tn = (N + 255) / 256, t128 = tn * ((M + 127) / 128), t64 = tn * ((M + 63) / 64);
   const bool wide = FMT == FMT_W4 ? tile_cost(t128, 28, 54) <= tile_cost(t64, 22, 40)
                                   : tile_cost(t128, 27, 45) <= tile_cost(t64, 17, 30);
-  return wide ? launch_t<FMT, 4>(P, sw, N, K, act, sx, asum, M, y, acc_out, s)
-              : launch_t<FMT, 2>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+#define QIFT_G(TC_, OP_) launch_t<FMT, TC_, OP_>(P, sw, N, K, act, sx, asum, M, y, acc_out, s)
+  if constexpr (FMT != FMT_POT)
+    if (asum) return wide ? QIFT_G(4, kCodes) : QIFT_G(2, kCodes);
+  // 16 x 8 x 7 x K stays below 2^31
+  if constexpr (FMT == FMT_W4)
+    if (K > (1 << 21)) return QIFT_G(2, kLevels1);
+  return wide ? QIFT_G(4, kLevels) : QIFT_G(2, kLevels);
+#undef QIFT_G
 }
 
 }  // namespace

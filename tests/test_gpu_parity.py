@@ -715,6 +715,26 @@ def test_tiled_gemm(Q, fmt, M, N, K):
         assert torch.equal(y.view(torch.int16), first.view(torch.int16))
 
 
+@pytest.mark.parametrize("K", [1 << 21, (1 << 21) + 64, 3 << 20])
+def test_tiled_gemm_w4_without_sums_very_long_k(Q, K):
+    # without code sums W4's operands are 16 times the levels up to K = 2^21 and the levels beyond, where 16 times
+    # the accumulator of extreme rows would leave int32 (49 x 3 x 2^20 x 16 > 2^31)
+    M, N = 65, 20
+    rng = np.random.default_rng(K)
+    L = rng.integers(-7, 8, (N, K), dtype=np.int8)
+    q = rng.integers(-7, 8, (M, K), dtype=np.int8)
+    L[0], L[1], q[0], q[64] = 7, -7, 7, -7
+    s_w = np.full(N, 2.0 ** -10, dtype=np.float16)
+    sx = np.full(M, 2.0 ** -10, dtype=np.float32)
+    pk = Q.pack_w4(dev(L), dev(s_w))
+    y, acc = run_linear(Q, pk, Q.QAct(dev(q), dev(sx)), M, N)
+    ref = np.zeros((M, N), dtype=np.int64)
+    for k in range(0, K, 1 << 18):   # 49 x 2^18 < 2^24: exact in fp32
+        ref += (q[:, k:k + (1 << 18)].astype(np.float32) @ L[:, k:k + (1 << 18)].T.astype(np.float32)).astype(np.int64)
+    assert np.array_equal(host(acc), ref)
+    assert np.array_equal(bits16(host(y)), bits16(olin.epilogue_fp32(ref.astype(np.int32), sx, s_w)))
+
+
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("K,b", [(64, 2), (64, 64), (128, 8), (192, 64), (256, 256), (384, 128), (640, 128), (768, 256),
                                  (1024, 32), (1024, 512), (1024, 1024), (1088, 64)])

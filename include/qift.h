@@ -310,17 +310,11 @@ int qift_w2a4_linear(const qift_packed_w *w, const int8_t *act_q, const float *a
  *   acc_out    out, nullable: int32 [M][N], the exact accumulators.
  *   workspace, workspace_bytes   optional device scratch (16-byte aligned).
  *              NULL / 0: no linear is split over K in a second launch.  With
- *              at least qift_workspace_bytes(w, M) bytes, where that is not 0
- *              (MNZ and PoT weights):
- *                M > 64, where the GEMM's tiles are few for the length of K:
- *                the int8 GEMM split over K, int32 partial sums of each K-range
- *                in the workspace, then added and the epilogue applied; else
- *                the unsplit GEMM;
- *                M <= 64, where the batch kernel does not take the linear: the
- *                same split GEMM from M = 33 on for wide or long weights, else
- *                (K > 4096, few 16-row tiles; up to 16 tokens only where the
- *                codes exceed the decode kernel's LDS) the decode linear split
- *                over K in the same way.
+ *              at least qift_workspace_bytes(w, M) bytes, where that is not 0,
+ *              the linear is split: int32 partial sums of each K-range in the
+ *              workspace, then added and the epilogue applied (the tiled GEMM
+ *              where its tiles are few for the length of K, from 33 tokens on,
+ *              W4 24; up to 47 tokens W2 of the longest K in the decode form).
  *              Either way the results are bit-identical.  A non-zero size
  *              below the query is QIFT_ERR_WORKSPACE.  The workspace is
  *              overwritten.
@@ -351,8 +345,7 @@ int qift_w2a4_lut_linear(const qift_packed_w *w, const uint16_t *lut, const int8
                          const float *act_scale, int64_t M, uint16_t *out, qift_stream_t stream);
 
 /* The W4 sibling (fmt QIFT_W4_SYM); same arguments and results.  The workspace of the _ex call is
- * used where qift_workspace_bytes is not 0: the int8 prefill GEMM split over K, as for W2 but from 24
- * tokens on for the wide and long linears. */
+ * used where qift_workspace_bytes is not 0: the tiled GEMM split over K. */
 int qift_w4a4_linear(const qift_packed_w *w, const int8_t *act_q, const float *act_scale,
                      int64_t M, uint16_t *out, qift_stream_t stream);
 int qift_w4a4_linear_ex(const qift_packed_w *w, const int8_t *act_q, const float *act_scale,
@@ -562,19 +555,13 @@ int qift_kv4_attention_decode_noalloc(const uint16_t *q, int64_t B, int32_t Hq, 
                                       const uint8_t *k_zeros, const uint8_t *v_codes, const float *v_scales,
                                       const uint8_t *v_zeros, uint16_t *out, qift_stream_t stream);
 
-/* Workspace bytes that the _ex calls ask for with this weight and M, 0 where none is used (host
- * query); the batch kernel and the unsplit GEMM accept the workspace and leave it alone.  N4 = N rounded up to 4; T = ceil(N / 256) * ceil(M / 64) prefill tiles; a count S of
- * K-ranges is recounted once the ranges are sized (ranges of ceil(steps / S) steps).
- *   M > 64, and from M = 33 (W4: 24) on N >= 16384 or N >= 4096 with K > 4096: the int8 GEMM split
- *     over S = min(ceil(512 / T), floor(512 / T), floor(steps / s0)) K-ranges when that is at least S0
- *     (W2: 256-k steps, s0 = 4, S0 = 2; W4: 128-k steps, s0 = 8, S0 = 3): S * M * N4 int32 partial
- *     sums (256-byte aligned), then S * M int32 code sums.
- *   M > 64 otherwise, MNZ and PoT: M * 3K/4 bytes and M * ceil(K / 8192) words and, for
- *     S = min(ceil(512 / T), floor(768 / T), floor(ceil(K / 256) / 4)) when that is at least 2, S * M * N4
- *     words at the next multiple of 256 bytes (accepted, and not used by the present kernels); W4: 0.
- *   M <= 64 otherwise, MNZ and PoT: the decode linear split over K, where it applies (K > 4096 and at most 680
- *     16-row tiles, N <= 10880; up to 16 tokens only where the codes exceed the decode kernel's LDS):
- *     S * M * N4 int32 partial sums (256-byte aligned) and S * M int32 code sums; W4: 0. */
+/* Workspace bytes that the _ex calls use for this weight and M (host query): 0 where the linear runs without a
+ * split over K, else S * M * N4 int32 partial sums (N4 = N rounded up to 4; 256-byte aligned), then S * M int32 code
+ * sums.  With T = ceil(N / 256) * ceil(M / 64) tiles, S is
+ *   for the tiled GEMM  min(ceil(512 / T), floor(512 / T), floor(steps / s0)) K-ranges (W2: 256-k steps, s0 = 4,
+ *                       from S = 2; W4: 128-k steps, s0 = 8, from S = 3),
+ *   for the W2 decode form  about 256 / ceil(N / 64) K-ranges (256-k units, at most 16 a range),
+ * recounted once the ranges are sized.  Which linears split follows measured times and may change; ask for each M. */
 size_t qift_workspace_bytes(const qift_packed_w *w, int64_t M);
 
 /* Static text for a status code. */

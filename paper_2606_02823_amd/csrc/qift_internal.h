@@ -50,11 +50,8 @@ hipError_t launch_rotate_quant_act(const uint16_t* x, int64_t M, int64_t K, int 
                                    hipStream_t s, bool bf16 = false);   // x fp16, or bf16 bits
 
 // Quantized linear (qift_linear.hip).  fmt selects the decode.  ws (nullable) serves the linears split over
-// K: gemm_split_workspace(fmt, N, M, K) bytes where that is not 0, else up to 64 tokens
-// skinny_workspace(fmt, N, K, M), else for MNZ and PoT weights a workspace of gemm_w2_workspace(N, M, K)
-// bytes is asked for (the sizes that callers have allocated so far) and not used.
-size_t gemm_split_workspace(int fmt, int64_t N, int64_t M, int64_t K);
-size_t gemm_w2_workspace(int64_t N, int64_t M, int64_t K);
+// K: linear_workspace(fmt, N, M, K) bytes, 0 where the kernel that takes the linear uses none (ws is null then).
+size_t linear_workspace(int fmt, int64_t N, int64_t M, int64_t K);
 hipError_t launch_linear(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,
                          const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
                          uint16_t* out, int32_t* acc_out, void* ws, hipStream_t s);
@@ -159,9 +156,7 @@ hipError_t launch_skinny(int fmt, const uint32_t* packed, const uint16_t* scales
                          const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
                          uint16_t* out, int32_t* acc_out, hipStream_t s);
 // The same split over K for W2 weights (MNZ, PoT) whose few 16-row tiles would leave every workgroup
-// reading all M x K codes for 16 or 32 rows: ws holds skinny_workspace(fmt, N, K, M) bytes (0: no split
-// for this linear, which the call then refuses).
-size_t skinny_workspace(int fmt, int64_t N, int64_t K, int64_t M);
+// reading all M x K codes for 16 or 32 rows (refused where route::skinny_split_plan has no split).
 hipError_t launch_skinny_split(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,
                                const int8_t* act_q, const float* act_scale, const int32_t* act_sum, int64_t M,
                                uint16_t* out, int32_t* acc_out, void* ws, hipStream_t s);

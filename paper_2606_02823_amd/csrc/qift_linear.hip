@@ -632,22 +632,15 @@ hipError_t launch_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t 
 
 }  // namespace
 
-size_t gemm_split_workspace(int fmt, int64_t N, int64_t M, int64_t K) {
-  const route::GemmSplit p = route::gemm_split_plan(fmt == FMT_W4, N, M, K);
-  return p.S > 1 ? split::part_bytes(p.S, M, N) + (size_t)p.S * (size_t)M * 4 : 0;
-}
-
-// M 3K/4 bytes, M ceil(K / 8192) words and, for the S K-ranges of three workgroups per CU where that is at
-// least two, the partial sums at the next multiple of 256 bytes.
-size_t gemm_w2_workspace(int64_t N, int64_t M, int64_t K) {
-  const size_t base = (size_t)M * (size_t)(3 * (K / 4)) + (size_t)M * (size_t)((K / 32 + 255) / 256) * 4;
-  const int64_t tiles = ((N + 255) / 256) * ((M + 63) / 64), KT = (K + 255) / 256;
-  int64_t S = (512 + tiles - 1) / tiles;
-  if (S > 768 / tiles) S = 768 / tiles;
-  if (S > KT / 4) S = KT / 4;
-  if (S < 2) return base;
-  const int64_t us = (KT + S - 1) / S;
-  return (base + 255) / 256 * 256 + split::part_bytes((int)((KT + us - 1) / us), M, N);
+size_t linear_workspace(int fmt, int64_t N, int64_t M, int64_t K) {
+  const bool w4 = fmt == FMT_W4;
+  int S = 0;
+  switch (route::choose(w4, N, K, M, codes_fit(fmt, M, N, K), true)) {
+    case route::kGemmSplit: S = route::gemm_split_plan(w4, N, M, K).S; break;
+    case route::kSkinnySplit: S = route::skinny_split_plan(w4, N, M, K).S; break;
+    default: return 0;
+  }
+  return split::part_bytes(S, M, N) + (size_t)S * (size_t)M * 4;
 }
 
 hipError_t launch_linear(int fmt, const uint32_t* packed, const uint16_t* scales, int64_t N, int64_t K,

@@ -54,7 +54,7 @@ struct SkSplit {
 
 inline SkSplit skinny_split_plan(bool w4, int64_t N, int64_t M, int64_t K) {
   SkSplit p;
-  if (w4 || M < 1 || M > kSkinnyMaxM || K > kSkinnyMaxK || N < 1 || K < 1) return p;
+  if (w4 || M < 1 || M > kSkSplitMaxM || K > kSkinnyMaxK || N < 1 || K < 1) return p;
   const int T = 4;
   const int64_t tiles = (N + 15) / 16, gx = (tiles + T - 1) / T;
   const int ut = (int)((K + 255) / 256);
@@ -138,10 +138,10 @@ inline bool take_batch(bool w4, int64_t N, int64_t K, int64_t M, bool gs, bool s
   return !codes_fit && M >= (w4 ? 12 : 9) && !ss;
 }
 
-// ws: a workspace of workspace bytes is given (the two split kernels need it).
+// ws: a workspace is given (the two split kernels need one).
 inline Kernel choose(bool w4, int64_t N, int64_t K, int64_t M, bool codes_fit, bool ws) {
   const bool gs = ws && gemm_split_plan(w4, N, M, K).S > 1;
-  const bool ss = ws && M <= kSkSplitMaxM && !(M <= kCodesMaxM && codes_fit) && skinny_split_plan(w4, N, M, K).S > 0;
+  const bool ss = ws && !(M <= kCodesMaxM && codes_fit) && skinny_split_plan(w4, N, M, K).S > 0;
   if (take_batch(w4, N, K, M, gs, ss, codes_fit)) return kBatch;
   // From 33 tokens on a wide linear that the batch kernel leaves runs the tiled GEMM rather than the skinny
   // kernel, whose workgroups each read all M x K codes (28672 x 4096 at 33 / 64 tokens: W2 22.9 -> 17.3 / 28.2 ->

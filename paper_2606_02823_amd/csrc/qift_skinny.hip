@@ -306,16 +306,6 @@ hipError_t launch_split_fmt(const SkSplit& p, const uint32_t* P, const uint16_t*
 
 }  // namespace
 
-size_t skinny_workspace(int fmt, int64_t N, int64_t K, int64_t M) {
-  if (M <= kCodesMaxM) {   // up to 16 tokens only where the decode kernel's LDS does not hold the codes
-    const size_t cs = fmt == FMT_MNZ ? codes_shmem_mnz(M, N, K) : fmt == FMT_POT ? codes_shmem_pot(M, N, K) : 0;
-    if (cs != 0 && cs <= 160 * 1024) return 0;
-  }
-  const SkSplit p = route::skinny_split_plan(fmt == FMT_W4, N, M, K);
-  if (p.S == 0) return 0;
-  return split_part_bytes(p, M, N) + (size_t)p.S * (size_t)M * 4;
-}
-
 hipError_t launch_skinny_split(int fmt, const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                                const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, void* ws,
                                hipStream_t s) {

@@ -227,69 +227,44 @@ def test_linear_validation(L):
     assert w2x(P(_pw()), None, A, None, 4, A, None, None, 0, None) == E_NULL
     assert w4x(P(_pw(fmt=qift.W2_MNZ)), A, A, None, 4, A, None, None, 0, None) == E_FORMAT
     assert L.qift_workspace_bytes(P(_pw()), 4) == 0
-    # the workspace that selects the FP4 x FP6 prefill kernel: MNZ and PoT at M > 64, M * 3K/4 bytes
-    K = _pw().K
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ)), 64) == 0
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ)), 65) == 65 * 3 * (K // 4) + 65 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_POT)), 65) == 65 * 3 * (K // 4) + 65 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W4_SYM)), 65) == 0
-    # 17..64 tokens: the skinny linear split over K when K > 4096 and its 16-row tiles are few (4 tiles
-    # per workgroup, S ranges of K for about 256 workgroups, at most two 256-k units per K-slice):
-    # S M N4 int32 partial sums (256-byte aligned), then S M int32 code sums; none for a gate|up width
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_POT, N=1000, K=14336)), 64) == 14 * 64 * 1000 * 4 + 14 * 64 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=1000, K=14336)), 64) == 14 * 64 * 1000 * 4 + 14 * 64 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_POT, N=1000, K=14336)), 17) == 952064 + 14 * 17 * 4
-    # a down shape (N >= 4096, K > 4096) from 33 tokens on: the prefill GEMM split over K (16 tiles -> S = 14)
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=4096, K=14336)), 64) == 14 * 64 * 4096 * 4 + 14 * 64 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=4096, K=14336)), 32) == 4 * 32 * 4096 * 4 + 4 * 32 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=1000, K=4096)), 64) == 0
-    # a gate|up width from 33 tokens on: the prefill GEMM split over K (112 tiles -> S = 4, W2 and W4);
-    # 32 tokens keep the skinny kernel (no workspace)
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=28672, K=4096)), 64) == 4 * 64 * 28672 * 4 + 4 * 64 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=28672, K=4096)), 32) == 0
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W4_SYM, N=28672, K=4096)), 64) == 4 * 64 * 28672 * 4 + 4 * 64 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W4_SYM, N=28672, K=4096)), 32) == 4 * 32 * 28672 * 4 + 4 * 32 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W4_SYM, N=28672, K=4096)), 23) == 0
-    # up to 16 tokens only where the decode kernel's LDS does not hold the codes (16 x 14336 does not,
-    # 4 x 14336 and 16 x 4096 do)
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=1000, K=14336)), 16) == 14 * 16 * 1000 * 4 + 14 * 16 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ, N=1000, K=14336)), 4) == 0
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_POT, N=1000, K=4096)), 16) == 0
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W4_SYM, N=1000, K=14336)), 64) == 0
-    # above 64 tokens, where the 256 x 64 GEMM tiles are few, the int8 GEMM is split over K: S ranges of
-    # at least 4 steps of 256 k, S = min(ceil(512 / tiles), 512 // tiles, steps // 4) when >= 2: S M N4
+    # the workspace of the linears split over K, 0 where the kernel that takes the linear uses none: S M N4
     # int32 partial sums (256-byte aligned), then S M int32 code sums
-    W = L.qift_workspace_bytes
-    # down at 128 tokens: 32 tiles, 56 steps -> S = 14
-    assert W(P(_pw(fmt=qift.W2_MNZ, N=4096, K=14336)), 128) == 14 * 128 * 4096 * 4 + 14 * 128 * 4
-    # gate|up at 65 tokens: 224 tiles -> S = 2
-    assert W(P(_pw(fmt=qift.W2_POT, N=28672, K=4096)), 65) == 2 * 65 * 28672 * 4 + 2 * 65 * 4
-    # ragged: 1000 rows (N4 = 1000), K = 4160 (17 steps, S = 4 of 5, 5, 5, 2), 96 tokens
-    assert W(P(_pw(fmt=qift.W2_POT, N=1000, K=4160)), 96) == 4 * 96 * 1000 * 4 + 4 * 96 * 4
-    # otherwise the FP4 x FP6 kernel's: FP6 codes and code sums, split over K itself where its tiles are
-    # few (S = min(ceil(512 / tiles), 768 // tiles, steps // 4) when >= 2), the partial sums following
-    # at the next multiple of 256 bytes.  q|k|v at 1024 tokens: 384 tiles -> S = 2; 65 x 5 tiles of
-    # 16400 x 2048 at 320 tokens -> S = 2; 448 tiles (gate|up at 256) and 512 (down at 2048): unsplit
-    assert W(P(_pw(fmt=qift.W2_MNZ, N=6144, K=4096)), 1024) == 1024 * 3072 + 1024 * 4 + 2 * 1024 * 6144 * 4
-    assert W(P(_pw(fmt=qift.W2_MNZ, N=16400, K=2048)), 320) == 320 * 1536 + 320 * 4 + 2 * 320 * 16400 * 4
-    assert W(P(_pw(fmt=qift.W2_MNZ, N=28672, K=4096)), 256) == 256 * 3072 + 256 * 4
-    assert W(P(_pw(fmt=qift.W2_MNZ, N=4096, K=14336)), 2048) == 2048 * 10752 + 2048 * 2 * 4
-    # W4 above 64 tokens: the int8 GEMM split over K where its tiles are few, S ranges of at least 8
-    # steps of 128 k, S = min(ceil(512 / tiles), 512 // tiles, steps // 8) when >= 3: S M N4 int32
-    # partial sums (256-byte aligned), then S M int32 code sums
-    assert W(P(_pw(fmt=qift.W4_SYM, N=4096, K=14336)), 128) == 14 * 128 * 4096 * 4 + 14 * 128 * 4
-    assert W(P(_pw(fmt=qift.W4_SYM, N=28672, K=4096)), 65) == 0        # 224 tiles: S = 2
-    assert W(P(_pw(fmt=qift.W4_SYM, N=4096, K=4096)), 512) == 4 * 512 * 4096 * 4 + 4 * 512 * 4
-    assert W(P(_pw(fmt=qift.W4_SYM, N=4096, K=14336)), 2048) == 0
-    assert W(P(_pw(fmt=qift.W4_SYM, N=4096, K=14336)), 64) == 14 * 64 * 4096 * 4 + 14 * 64 * 4
-    assert W(P(_pw(fmt=qift.W4_SYM, N=4096, K=14336)), 24) == 14 * 24 * 4096 * 4 + 14 * 24 * 4   # W4 from 24
-    assert W(P(_pw(fmt=qift.W4_SYM, N=4096, K=14336)), 23) == 0
-    # FP6 codes (M 3K/4 bytes), then one int32 code sum per token and 256 groups of 32 k
-    need = 100 * 3 * (K // 4) + 100 * 4
-    assert L.qift_workspace_bytes(P(_pw(fmt=qift.W2_MNZ)), 100) == need
-    assert w2x(P(_pw(fmt=qift.W2_MNZ)), A, A, A, 100, A, None, A, need - 16, None) == E_WS
-    assert w2x(P(_pw(fmt=qift.W2_MNZ)), A, A, A, 100, A, None, None, need, None) == E_WS
-    assert w2x(P(_pw(fmt=qift.W2_MNZ)), A, A, A, 100, A, None, MIS, need, None) == E_ALIGN
+    W = lambda M, N, K, fmt=qift.W2_MNZ: L.qift_workspace_bytes(P(_pw(fmt=fmt, N=N, K=K)), M)
+    size = lambda S, M, N: -(-(S * M * (-(-N // 4) * 4) * 4) // 256) * 256 + S * M * 4
+    for fmt in (qift.W2_MNZ, qift.W2_POT, qift.W4_SYM):
+        for M, N, K in ((64, 512, 256), (65, 512, 256), (100, 512, 256), (64, 1000, 4096), (64, 1000, 14336),
+                        (64, 4096, 14336), (64, 28672, 4096), (32, 28672, 4096), (4, 1000, 14336), (16, 1000, 4096),
+                        (1024, 6144, 4096), (320, 16400, 2048), (256, 28672, 4096), (2048, 4096, 14336),
+                        (65, 28672, 4096), (48, 1000, 14336)):
+            assert W(M, N, K, fmt) == 0, (M, N, K, fmt)   # batch, GEMM, codes
+    # above 64 tokens the GEMM split over K: S = min(ceil(512 / tiles), 512 // tiles, steps // s0) ranges (W2 256-k
+    # steps, s0 = 4, from 2; W4 128-k steps, s0 = 8, from 3).  4096 x 14336 at 128 tokens: 32 tiles, 56 steps -> 14;
+    # 4096 x 4096 at 100: 32 tiles, 16 steps -> 4, at 300 80 tiles: unsplit; ragged: 1000 x 4160, 17 steps -> 4 of 5, 5, 5, 2
+    for fmt in (qift.W2_MNZ, qift.W2_POT):
+        assert W(128, 4096, 14336, fmt) == size(14, 128, 4096)
+        assert W(100, 4096, 4096, fmt) == size(4, 100, 4096)
+        assert W(300, 4096, 4096, fmt) == 0
+        assert W(96, 1000, 4160, fmt) == size(4, 96, 1000)
+        # and below, wide and long (24832 x 8192 at 40: 97 tiles, 32 steps -> 5)
+        assert W(40, 24832, 8192, fmt) == size(5, 40, 24832)
+        # up to 47 tokens the decode form for the longest K (4 16-row tiles a workgroup, 1000 rows: 16 workgroups,
+        # S = 16 -> 14 ranges of 4 units); up to 16 only where the decode kernel's LDS does not hold the codes
+        for M in (11, 16, 17, 32, 47):
+            assert W(M, 1000, 14336, fmt) == size(14, M, 1000)
+        assert W(32, 4096, 14336, fmt) == size(4, 32, 4096)
+    assert W(128, 4096, 14336, qift.W4_SYM) == size(14, 128, 4096)
+    assert W(256, 4096, 4096, qift.W4_SYM) == size(4, 256, 4096)
+    assert W(512, 4096, 4096, qift.W4_SYM) == 0                      # 128 tiles of a short K
+    assert W(24, 4096, 14336, qift.W4_SYM) == size(14, 24, 4096)     # W4 from 24 tokens
+    assert W(23, 4096, 14336, qift.W4_SYM) == 0
+    # a size below the query is refused, one above it or where none is needed accepted (as far as its alignment)
+    need = W(100, 4096, 4096)
+    big = _pw(fmt=qift.W2_MNZ, N=4096, K=4096)
+    assert w2x(P(big), A, A, A, 100, A, None, A, need - 16, None) == E_WS
+    assert w2x(P(big), A, A, A, 100, A, None, None, need, None) == E_WS
+    assert w2x(P(big), A, A, A, 100, A, None, MIS, need, None) == E_ALIGN
+    assert w2x(P(_pw(fmt=qift.W2_MNZ)), A, A, A, 100, A, None, None, 64, None) == E_WS
+    assert w2x(P(_pw(fmt=qift.W2_MNZ)), A, A, A, 100, A, None, MIS, 1 << 20, None) == E_ALIGN
 
 
 def test_fused_validation(L):

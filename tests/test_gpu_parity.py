@@ -128,119 +128,87 @@ def test_linear_ragged(Q, fmt, M):
     assert torch.equal(y3.view(torch.int16), y.view(torch.int16))
 
 
-@pytest.mark.parametrize("fmt", [levels.FMT_W2_MNZ, levels.FMT_W2_POT])
-@pytest.mark.parametrize("M,N,K", [(65, 1000, 1088), (130, 1000, 1088), (300, 1000, 4096), (200, 1000, 14336),
-                                   (96, 1000, 4160), (320, 16400, 2048)])
-def test_w2_prefill_int8_and_fp4_paths(Q, fmt, M, N, K):
-    # W2 (MNZ, PoT) at M > 64, ragged rows and tokens, K with a partial last step; bit-identical to the
-    # oracle on every path:
-    #   no workspace: the int8 GEMM;
-    #   a workspace of workspace_bytes where the 256 x 64 tiles are few: the int8 GEMM split over K
-    #   (S = min(ceil(512 / tiles), 512 // tiles, steps // 4) >= 2 ranges of 256-k steps; K = 4160 has
-    #   17 steps: ranges of 5, 5, 5 and 2, the last one ending in a partial step);
-    #   otherwise the FP4 x FP6 GEMM (FP6 activations in the workspace; the MNZ codes as c / 2, the PoT
-    #   levels +-1, +-4 as E2M1 values), itself split over K where S = min(ceil(512 / tiles),
-    #   768 // tiles, steps // 4) >= 2 (16400 x 2048 at 320 tokens: 325 tiles, two ranges).
-    b = 64
-    L = synth.draw_levels(fmt, N, K, cfg=97, layer=M + fmt)
-    s_w = synth.draw_scales(fmt, N, cfg=97, layer=M + fmt)
-    x = synth.activations_fp16(97, M, 0, M, K, K // 100, 30.0)
-    pk = pack_dev(Q, L, s_w, fmt)
-    act = Q.rotate_quant_act(dev(x), b)
-    q_ref, sx_ref = check_act(act, x, b)
-    KT, tiles, N4 = -(-K // 256), -(-N // 256) * -(-M // 64), -(-N // 4) * 4
-
-    def ranges(S):
-        if S < 2:
-            return 1
-        us = -(-KT // S)
-        return -(-KT // us)
-
-    S8 = ranges(min(-(-512 // tiles), 512 // tiles, KT // 4))
-    if S8 > 1:
-        expect = -(-(S8 * M * N4 * 4) // 256) * 256 + S8 * M * 4
-    else:
-        expect = M * 3 * (K // 4) + 4 * M * (-(-(K // 32) // 256))
-        S4 = ranges(min(-(-512 // tiles), 768 // tiles, KT // 4))
-        if S4 > 1:
-            expect = -(-expect // 256) * 256 + -(-(S4 * M * N4 * 4) // 256) * 256
-    assert Q.workspace_bytes(pk, M) == expect
-    for ws in (None, torch.empty(Q.workspace_bytes(pk, M), dtype=torch.uint8, device="cuda")):
-        for use_sum in (False, True):
-            y, acc = run_linear(Q, pk, act, M, N, use_sum=use_sum, workspace=ws)
-            check_linear(y, acc, L, q_ref, sx_ref, s_w)
+def split_bytes(S, M, N):
+    return -(-(S * M * (-(-N // 4) * 4) * 4) // 256) * 256 + S * M * 4
 
 
-@pytest.mark.parametrize("M,N,K", [(65, 300, 4160), (200, 300, 4160), (128, 1000, 14336), (96, 4096, 1088),
-                                   (130, 2064, 8192), (40, 16400, 4160), (64, 16384, 2048), (48, 4096, 14336),
-                                   (24, 4096, 14336), (30, 28672, 4096)])
-def test_w4_prefill_split_over_k(Q, M, N, K):
-    # W4 above 64 tokens with a workspace of workspace_bytes: where the 256 x 64 tiles are few the int8
-    # GEMM is split over K (S >= 3 ranges of at least 8 steps of 128 k, about 512 workgroups, at most 512):
-    # K = 4160 has 33 steps (ranges of 9, 9, 9 and 6, the last step partial); K = 1088 has 9 steps, too
-    # few to split (workspace_bytes 0).  From 24 tokens on a gate|up width (N >= 16384) or a down shape
-    # (N >= 4096, K > 4096) takes the same split instead of the skinny kernel.  Bit-identical to the oracle and to the call without a
-    # workspace, with and without the quantizer's code sums.
-    fmt = levels.FMT_W4_SYM
-    L = synth.draw_levels(fmt, N, K, cfg=95, layer=M)
-    s_w = synth.draw_scales(fmt, N, cfg=95, layer=M)
-    x = synth.activations_fp16(95, M, 0, M, K, 9, 30.0)
-    pk = pack_dev(Q, L, s_w, fmt)
-    act = Q.rotate_quant_act(dev(x), 64)
-    q_ref, sx_ref = check_act(act, x, 64)
-    KT, tiles = -(-K // 128), -(-N // 256) * -(-M // 64)
-    S = min(-(-512 // tiles), 512 // tiles, KT // 8)
-    need = Q.workspace_bytes(pk, M)
-    if S >= 3:
-        us = -(-KT // S)
-        S = -(-KT // us)
-        assert need == -(-(S * M * (-(-N // 4) * 4) * 4) // 256) * 256 + S * M * 4
-    else:
-        assert need == 0
-    ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
-    for use_sum in (False, True):
-        y, acc = run_linear(Q, pk, act, M, N, use_sum=use_sum, workspace=ws if need else None)
-        check_linear(y, acc, L, q_ref, sx_ref, s_w)
-        y0, acc0 = run_linear(Q, pk, act, M, N, use_sum=use_sum)
-        assert torch.equal(acc, acc0) and torch.equal(y.view(torch.int16), y0.view(torch.int16))
+def gemm_ranges(M, N, K, fmt):
+    """K-ranges of the split GEMM: 256-k steps, at least 4 a range (W4 128 and 8), about 512 workgroups."""
+    bk, s0 = (128, 8) if fmt == levels.FMT_W4_SYM else (256, 4)
+    KT, tiles = -(-K // bk), -(-N // 256) * -(-M // 64)
+    S = min(-(-512 // tiles), 512 // tiles, KT // s0)
+    return -(-KT // -(-KT // S))
 
 
-@pytest.mark.parametrize("fmt", [levels.FMT_W2_MNZ, levels.FMT_W2_POT])
-@pytest.mark.parametrize("M,N,K", [(17, 1000, 1088), (32, 1000, 14336), (33, 4096, 4096), (64, 1000, 14336),
-                                   (64, 4096, 14336), (20, 2064, 8192), (40, 300, 16384), (64, 6144, 4096),
-                                   (47, 28672, 4096), (16, 1000, 14336), (13, 4096, 14336), (16, 1000, 4096),
-                                   (32, 28672, 4096), (40, 16400, 4160)])
-def test_skinny_split_over_k(Q, fmt, M, N, K):
-    # 17..64 tokens with a workspace of workspace_bytes, and up to 16 where the decode kernel's LDS does
-    # not hold the codes (16 or 13 tokens of 14336): a linear with K > 4096 and few 16-row tiles runs
-    # split over K (int32 partial sums of each K-range in the workspace, then added and the epilogue
-    # applied); K <= 4096 needs no split (workspace_bytes 0).  From 33 tokens on a gate|up width (N >=
-    # 16384) or a down shape (N >= 4096, K > 4096) takes the prefill GEMM split over K instead (S = min(ceil(512 / tiles), 512 // tiles,
-    # steps // 4) ranges of 256-k steps over 256 x 64 tiles).  Bit-identical to the oracle and to the call
-    # without a workspace, with and without the quantizer's code sums.
-    b = 4096 if K % 4096 == 0 else (2048 if K % 2048 == 0 else 64)
-    L = synth.draw_levels(fmt, N, K, cfg=98, layer=M + fmt)
-    s_w = synth.draw_scales(fmt, N, cfg=98, layer=M + fmt)
-    x = synth.activations_fp16(98, M, 0, M, K, max(1, K // 100), 30.0)
+def skinny_ranges(N, K):
+    """K-ranges of the skinny split: 4 16-row tiles a workgroup, about 256 workgroups, at most 16 units a range."""
+    gx, ut = -(-(-(-N // 16)) // 4), -(-K // 256)
+    S = min(max((256 + gx // 2) // gx, -(-ut // 16)), ut)
+    return -(-ut // -(-ut // S))
+
+
+def check_split(Q, M, N, K, b, fmt, cfg, form):
+    """The linear with the workspace it asks for and without one: bit-identical to the oracle, with and without the
+    quantizer's code sums.  form: the split that the workspace's size shows (None: the size is 0)."""
+    L = synth.draw_levels(fmt, N, K, cfg=cfg, layer=M + fmt)
+    s_w = synth.draw_scales(fmt, N, cfg=cfg, layer=M + fmt)
+    x = synth.activations_fp16(cfg, M, 0, M, K, max(1, K // 100), 30.0)
     pk = pack_dev(Q, L, s_w, fmt)
     act = Q.rotate_quant_act(dev(x), b)
     q_ref, sx_ref = check_act(act, x, b)
     need = Q.workspace_bytes(pk, M)
-    if M >= 33 and (N >= 16384 or (N >= 4096 and K > 4096)):
-        tiles, KT = -(-N // 256), -(-K // 256)
-        S = min(-(-512 // tiles), 512 // tiles, KT // 4)
-        S = -(-KT // -(-KT // S))
-        assert need == -(-(S * M * (-(-N // 4) * 4) * 4) // 256) * 256 + S * M * 4
-    else:
-        # the skinny split rule: K > 4096, 4 tiles per workgroup, S = 256 / workgroups rounded, from S = 2
-        gx = -(-(-(-N // 16)) // 4)
-        assert (need > 0) == (K > 4096 and (256 + gx // 2) // gx >= 2)
-    ws = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+    S = {None: 0, "gemm": gemm_ranges(M, N, K, fmt), "skinny": skinny_ranges(N, K)}[form]
+    assert need == (split_bytes(S, M, N) if form else 0)
+    # every row up to 4096, beyond them the first and last and 300 between
+    rows = None if N <= 4096 else np.unique(np.concatenate([np.arange(8), np.random.default_rng(N).choice(N, 300),
+                                                            np.arange(N - 8, N)]))
     y0, acc0 = run_linear(Q, pk, act, M, N)
-    check_linear(y0, acc0, L, q_ref, sx_ref, s_w)
+    check_linear(y0, acc0, L, q_ref, sx_ref, s_w, rows=rows)
+    # a workspace that is not needed is accepted and left alone
+    ws = torch.full((need if need else 4096,), 0x5A, dtype=torch.uint8, device="cuda")
     for use_sum in (False, True):
         y, acc = run_linear(Q, pk, act, M, N, use_sum=use_sum, workspace=ws)
         assert torch.equal(acc, acc0) and torch.equal(y.view(torch.int16), y0.view(torch.int16))
+    if not need:
+        assert bool((ws == 0x5A).all())
+
+
+@pytest.mark.parametrize("fmt", [levels.FMT_W2_MNZ, levels.FMT_W2_POT])
+@pytest.mark.parametrize("M,N,K,form", [(65, 1000, 1088, None), (130, 1000, 1088, None), (300, 1000, 4096, "gemm"),
+                                        (200, 1000, 14336, "gemm"), (96, 1000, 4160, "gemm"), (320, 16400, 2048, None)])
+def test_w2_prefill_with_and_without_split(Q, fmt, M, N, K, form):
+    # W2 (MNZ, PoT) at M > 64, ragged rows and tokens, K with a partial last step; the split GEMM where the 256 x 64
+    # tiles are few for the length of K (K = 4160 has 17 steps: ranges of 5, 5, 5 and 2, the last one ending in a
+    # partial step), else the unsplit one
+    check_split(Q, M, N, K, 64, fmt, 97, form)
+
+
+@pytest.mark.parametrize("M,N,K,form", [(65, 300, 4160, "gemm"), (200, 300, 4160, "gemm"), (128, 1000, 14336, "gemm"),
+                                        (96, 4096, 1088, None), (130, 2064, 8192, "gemm"), (40, 16400, 4160, None),
+                                        (64, 16384, 2048, None), (48, 4096, 14336, None), (24, 4096, 14336, "gemm"),
+                                        (30, 28672, 4096, None), (33, 4096, 16384, "gemm")])
+def test_w4_prefill_split_over_k(Q, M, N, K, form):
+    # W4 with a workspace: the GEMM split over K (S >= 3 ranges of at least 8 steps of 128 k; K = 4160 has 33 steps:
+    # ranges of 9, 9, 9 and 6, the last step partial; K = 1088 has 9, too few), from 24 tokens on for long linears
+    # that the batch kernel leaves
+    check_split(Q, M, N, K, 64, levels.FMT_W4_SYM, 95, form)
+
+
+@pytest.mark.parametrize("fmt", [levels.FMT_W2_MNZ, levels.FMT_W2_POT])
+@pytest.mark.parametrize("M,N,K,form", [(17, 1000, 1088, None), (32, 1000, 14336, "skinny"), (33, 4096, 4096, None),
+                                        (64, 1000, 14336, None), (64, 4096, 14336, None), (20, 2064, 8192, None),
+                                        (40, 300, 16384, "skinny"), (64, 6144, 4096, None), (47, 28672, 4096, None),
+                                        (16, 1000, 14336, "skinny"), (13, 4096, 14336, "skinny"), (16, 1000, 4096, None),
+                                        (32, 28672, 4096, None), (40, 16400, 4160, None),
+                                        # one, two and four token tiles; ranges that end inside the last unit
+                                        (10, 1000, 16384, "skinny"), (11, 999, 16320, "skinny"), (17, 2048, 11008, "skinny"),
+                                        (33, 1001, 14400, "skinny"), (47, 1000, 14336, "skinny"),
+                                        (40, 24832, 8192, "gemm"), (33, 22016, 11008, "gemm")])
+def test_skinny_split_over_k(Q, fmt, M, N, K, form):
+    # up to 64 tokens with a workspace: the skinny split for the longest K with few 16-row tiles (up to 16 tokens
+    # where the decode kernel's LDS does not hold the codes), the split GEMM for wide and long linears
+    b = 4096 if K % 4096 == 0 else (2048 if K % 2048 == 0 else 64)
+    check_split(Q, M, N, K, b, fmt, 98, form)
 
 
 @pytest.mark.parametrize("fmt", FMTS)

@@ -65,7 +65,8 @@ SPEC_BF16 = 1 << 16   # QIFT_SPEC_BF16: the tokens are bf16 values
 
 
 def spec(K: int, block: int, clip=(1, 1), bf16: bool = False) -> HadamardSpec:
-    if clip == (1, 1) and not bf16:
+    # (a pair of any kind is taken; only a plain tuple compares to a truth value)
+    if type(clip) is tuple and clip == (1, 1) and not bf16:
         return HadamardSpec(K, block, 0)
     return HadamardSpec(K, block, clip_flags(*clip) | (SPEC_BF16 if bf16 else 0))
 

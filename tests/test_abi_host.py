@@ -71,6 +71,14 @@ def test_spec_layout_and_clip_flags():
     assert "#define QIFT_CLIP(num, den) ((int32_t)((((num) & 0xFF) << 8) | ((den) & 0xFF)))" in text
 
 
+def test_spec_takes_a_clip_pair_of_any_kind():
+    for pair in ((1, 1), (9, 10)):
+        want = qift.spec(256, 64, clip=pair).flags
+        for kind in (list, np.array, lambda p: np.array(p, dtype=np.float64)):
+            assert qift.spec(256, 64, clip=kind(pair)).flags == want
+            assert qift.spec(256, 64, clip=kind(pair), bf16=True).flags == want | qift.SPEC_BF16
+
+
 def test_quantize_weights_validation(L):
     f = L.qift_quantize_weights
     mnz, pot, w4 = qift.W2_MNZ, qift.W2_POT, qift.W4_SYM

@@ -145,12 +145,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The handle of the current device's current stream without building a Stream object: names of torch's own that
+# a release may drop; the public call gives the same handle.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
     if stream is not None:
         return stream.cuda_stream
-    if torch.cuda.is_initialized():
-        # the handle of the current device's current stream without building a Stream object
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_raw_device())
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -328,6 +328,20 @@ def test_device_error_api_validation(L):
     assert L.qift_set_wait_limit(0) == OK     # back to the default
 
 
+def test_stream_handle_without_the_private_names(monkeypatch):
+    # torch's private accessors are a shortcut: without them the public call gives the handle
+    class Current:
+        cuda_stream = 0x5150
+
+    monkeypatch.setattr(qift.torch.cuda, "current_stream", lambda: Current)
+    monkeypatch.setattr(qift.torch.cuda, "is_initialized", lambda: True)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(qift.torch._C, name, raising=False)
+    monkeypatch.setattr(qift, "_raw_stream", None, raising=False)
+    assert qift._stream() == 0x5150
+    assert qift._stream(Current) == 0x5150
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(qift, "LIB_PATH", str(tmp_path / "missing.so"))
     monkeypatch.setattr(qift, "_lib", None)

@@ -100,7 +100,8 @@ typedef struct {
   int32_t layout;          /* QIFT_LAYOUT_V1                                  */
   int64_t N, K;            /* output and input features                       */
   const uint32_t *packed;  /* words, qift_packed_bytes(fmt, N, K) bytes       */
-  const uint16_t *scales;  /* fp16 s_w[N]; for MNZ this is the half scale s/2 */
+  const uint16_t *scales;  /* fp16 s_w[N]; for MNZ this is the half scale s/2 (the decode chain reads
+                              the aligned 4 bytes that hold the last one of an odd N) */
 } qift_packed_w;
 
 /*

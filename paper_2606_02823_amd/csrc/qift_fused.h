@@ -389,6 +389,7 @@ __global__ __launch_bounds__((fused_threads<NTILES, CODES>())) void k_fused_deco
       red[(j * NS + slice) * 64 + lane] = s;
     }
   }
+  if (wave < T) swq = odd_last_scale(swq, sw, n_st, N);
   __syncthreads();
   if (wave < T) {
     const int j = wave;

@@ -191,6 +191,17 @@ __device__ __forceinline__ void store4(const v4i& D, int m, int n0, int N, float
   }
 }
 
+// The scales s_w[n0..n0+3] as range-checked dword loads returned them, with the last channel of an odd N
+// put in: its dword ends past the array, so those loads return zero for it (only that channel's lanes load).
+__device__ __forceinline__ uint2 odd_last_scale(uint2 swq, const uint16_t* __restrict__ sw, int n0, int N) {
+  if ((N & 1) && n0 < N && n0 + 4 > N) {
+    const uint32_t last = sw[N - 1];
+    if (N & 2) swq.y = last;   // N = 4 i + 3: channel n0 + 2
+    else swq.x = last;         // N = 4 i + 1: channel n0
+  }
+  return swq;
+}
+
 // store4 with the four fp16 scales s_w[n0..n0+3] already in registers (swq,
 // low half first; zeros past N).
 template <int FMT>

@@ -100,6 +100,17 @@ def llama31_layers(fmt, layers, seed0=0):
     return specs
 
 
+@pytest.mark.parametrize("fmt", [levels.FMT_W2_MNZ, levels.FMT_W2_POT, levels.FMT_W4_SYM])
+@pytest.mark.parametrize("N0,N1", [(4097, 277), (4099, 70001), (6145, 1)])
+def test_chain_odd_row_counts(Q, fmt, N0, N1):
+    """Links of an odd number of rows: the last channel's scale shares its dword with the end of its array
+    (70001 rows: several chunks of tiles in a workgroup, whose scales take another path)."""
+    specs = [Spec(fmt, N0, 4096, 4096, -1, 0, 30), Spec(fmt, N1, 4096, 2048, 0, 0, 31)]
+    chain, _ = build(Q, specs, 2)
+    for r in range(2):
+        check_run(Q, chain, specs, synth.activations_fp16(83, r, 0, 2, 4096, 41, 30.0))
+
+
 def test_chain_two_llama31_layers_mnz(Q):
     """Two LLaMA-3.1-8B decode layers chained (8 links, the real shapes and dependencies): bit-exact,
     on three runs with different inputs (the second and third would expose stale reads)."""

@@ -212,6 +212,31 @@ def test_skinny_split_over_k(Q, fmt, M, N, K, form):
 
 
 @pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("K", [384, 4096, 6144, 14336])
+@pytest.mark.parametrize("N", [1, 3, 273, 277, 279, 4097])
+def test_odd_row_counts(Q, fmt, K, N):
+    # the last channel of an odd N shares its dword with the end of the scales' array: every kernel's token range,
+    # the fused entry (1-4 tokens) and the linear on codes
+    b = 128 if K == 384 else 2048
+    L = synth.draw_levels(fmt, N, K, cfg=89, layer=N)
+    s_w = synth.draw_scales(fmt, N, cfg=89, layer=N)
+    pk = pack_dev(Q, L, s_w, fmt)
+    rows = None if N < 4096 else np.unique(np.concatenate([np.arange(64), np.arange(N - 64, N)]))
+    for M in (1, 4, 16, 20, 48, 70):
+        x = synth.activations_fp16(89, M, 0, M, K, 5, 30.0)
+        act = Q.rotate_quant_act(dev(x), b)
+        q_ref, sx_ref = check_act(act, x, b)
+        for use_sum in (False, True):
+            y, acc = run_linear(Q, pk, act, M, N, use_sum=use_sum)
+            check_linear(y, acc, L, q_ref, sx_ref, s_w, rows=rows)
+        if M <= 4:
+            acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+            y = Q.rotate_quant_linear(pk, dev(x), b, acc_out=acc)
+            torch.cuda.synchronize()
+            check_linear(y, acc, L, q_ref, sx_ref, s_w, rows=rows)
+
+
+@pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("M,K", [(1, 20480), (9, 20480), (16, 32768)])
 def test_linear_long_k(Q, fmt, M, K):
     # K beyond the decode-on-codes kernel's limit: codes staged in LDS (M = 1) or read from HBM

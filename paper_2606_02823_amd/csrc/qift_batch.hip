@@ -7,8 +7,8 @@
 // and waits only on its own load counter.  RJ is chosen so that the grid is about one workgroup per CU:
 // the weights are read once, each CU reads the M x K codes once, and the time hardly grows with the tokens.
 // What bounds it at these sizes is latency: launch, the first loads from HBM, a few steps (a 4096-k row is
-// 32 steps over 4 or 8 waves), the sum of the slices, and the address unit, which takes about 55 cycles for
-// each kilobyte of codes: so the loads of a step cover 16, 32, 48 or 64 tokens (NA; 4096 x 14336 at 16 tokens
+// 32 steps over 4 or 8 waves), the sum of the slices, and the address unit, which takes 36 to 70 cycles for
+// each kilobyte of codes or weights (busy 28-59 % of the time at K = 4096, 80 % at 11008 and 14336): so the loads of a step cover 16, 32, 48 or 64 tokens (NA; 4096 x 14336 at 16 tokens
 // 11.5 -> 10.2 us against 32), and RJ is as large as the grid allows.  Eight waves where their registers allow (32 RJ TC
 // accumulators each), four otherwise.  Four line groups of weights in flight instead of two measured slower
 // (12288 x 4096 at 16 tokens 8.2 -> 9.1 us).

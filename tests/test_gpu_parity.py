@@ -14,6 +14,8 @@ import torch
 from oracle import hadamard, levels, linear as olin, pack as opack, quant
 from paper_2606_02823_amd import synth
 
+from route_probe import ask
+
 pytestmark = pytest.mark.gpu
 
 FMTS = [levels.FMT_W2_MNZ, levels.FMT_W2_POT, levels.FMT_W4_SYM]
@@ -128,6 +130,12 @@ def test_linear_ragged(Q, fmt, M):
     assert torch.equal(y3.view(torch.int16), y.view(torch.int16))
 
 
+def check_route(kernel, fmt, M, N, K):
+    """The linear without a workspace runs the kernel that a test is about (up to 16 tokens: codes of 16 more bytes a
+    token within about 130 KB are in the decode kernel's LDS)."""
+    assert ask([(fmt == levels.FMT_W4_SYM, N, K, M, K <= 16384 and M * (K + 16) <= 130 * 1024, 0)])[0][0] == kernel
+
+
 def split_bytes(S, M, N):
     return -(-(S * M * (-(-N // 4) * 4) * 4) // 256) * 256 + S * M * 4
 
@@ -194,6 +202,21 @@ def test_w4_prefill_split_over_k(Q, M, N, K, form):
     check_split(Q, M, N, K, 64, levels.FMT_W4_SYM, 95, form)
 
 
+SKINNY_SHAPES = [(f, *shape) for fmts, shapes in (
+    (FMTS, [(17, 300, 1088), (23, 999, 4736), (32, 5000, 2112), (32, 12300, 1088), (31, 12300, 2112), (47, 300, 2112),
+            (64, 300, 1088), (40, 5000, 2112), (64, 12300, 1088), (40, 12300, 2112)]),
+    ([levels.FMT_W2_MNZ, levels.FMT_W2_POT], [(20, 40968, 4160)]),
+    ([levels.FMT_W4_SYM], [(20, 3000, 11008), (27, 2600, 16384)])) for f in fmts for shape in shapes]
+
+
+@pytest.mark.parametrize("fmt,M,N,K", SKINNY_SHAPES)
+def test_skinny_linear(Q, fmt, M, N, K):
+    # the skinny kernel unsplit: two and four token tiles, one to four row tiles a workgroup, one to eight 256-k units
+    # a slice, rows, tokens and k that end inside a tile
+    check_route("skinny", fmt, M, N, K)
+    check_split(Q, M, N, K, 64, fmt, 88, None)
+
+
 @pytest.mark.parametrize("fmt", [levels.FMT_W2_MNZ, levels.FMT_W2_POT])
 @pytest.mark.parametrize("M,N,K,form", [(17, 1000, 1088, None), (32, 1000, 14336, "skinny"), (33, 4096, 4096, None),
                                         (64, 1000, 14336, None), (64, 4096, 14336, None), (20, 2064, 8192, None),
@@ -237,10 +260,12 @@ def test_odd_row_counts(Q, fmt, K, N):
 
 
 @pytest.mark.parametrize("fmt", FMTS)
-@pytest.mark.parametrize("M,K", [(1, 20480), (9, 20480), (16, 32768)])
+@pytest.mark.parametrize("M,K", [(1, 20480), (7, 20480), (9, 20480), (11, 20480), (16, 32768)])
 def test_linear_long_k(Q, fmt, M, K):
-    # K beyond the decode-on-codes kernel's limit: codes staged in LDS (M = 1) or read from HBM
+    # K beyond the decode-on-codes kernel's limit: the decode kernels with codes staged in LDS (M = 1) or read from
+    # memory (7 tokens, W4 to 11), then the batch kernel
     N, b = 300, 4096
+    check_route("batch" if M >= (12 if fmt == levels.FMT_W4_SYM else 9) else "decode", fmt, M, N, K)
     L = synth.draw_levels(fmt, N, K, cfg=91, layer=M)
     s_w = synth.draw_scales(fmt, N, cfg=91, layer=M)
     x = synth.activations_fp16(91, M, 0, M, K, K // 100, 30.0)
@@ -317,7 +342,8 @@ def test_rotate_quant_act_blocks(Q, K, b):
                                    (3, 12288, 4096), (64, 8192, 256)])
 def test_rotate_quant_act_tile_parallel(Q, M, K, b):
     # up to 256 tokens of several 4096-tiles the tiles are rotated at once by groups of four waves,
-    # one token per workgroup; from 257 tokens on by the persistent kernel: the same codes either way
+    # one token per workgroup; from 257 tokens on four tiles by two groups, fewer by the persistent kernel: the
+    # same codes either way
     x = synth.activations_fp16(93, M, b, M, K, max(1, K // 100), 30.0)
     if M > 2:
         x[1] = 0                                            # all-zero token
@@ -674,7 +700,7 @@ def test_hbm_read_probe_reads_every_word(Q, nwords):
 
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("M,N,K", [(65, 264, 64), (128, 256, 128), (97, 520, 576), (129, 1000, 1536), (200, 999, 1664),
-                                   (64, 16400, 704), (33, 16384, 1088), (130, 28672, 640), (200, 22016, 1536),
+                                   (64, 16400, 704), (33, 16385, 1088), (130, 28672, 640), (200, 22016, 1536),
                                    (256, 16390, 320)])
 def test_tiled_gemm(Q, fmt, M, N, K):
     # The tiled GEMM's edges: K from half a step (128 k) over partial and odd line groups (512 k of W2,
@@ -683,6 +709,7 @@ def test_tiled_gemm(Q, fmt, M, N, K):
     # mod 8); 64-token tiles (few tiles) and 128-token tiles (the last three shapes).  Run once on warm
     # and once on cold caches, where the loads arrive late.  Bit-identical to the oracle (all rows of the
     # small shapes, 200 of the wide ones) with and without accumulators and code sums.
+    check_route("gemm", fmt, M, N, K)
     b = 64
     L = synth.draw_levels(fmt, N, K, cfg=94, layer=M + fmt)
     s_w = synth.draw_scales(fmt, N, cfg=94, layer=M + fmt)
@@ -762,17 +789,25 @@ def test_fused_one_wave_per_token(Q, fmt, K, b):
     assert np.array_equal(host(acc), olin.int_dot(L, q_ref))
 
 
-@pytest.mark.parametrize("fmt", FMTS)
-@pytest.mark.parametrize("M,N,K", [(17, 4100, 4096), (16, 4096, 4096), (15, 300, 4736), (9, 6200, 4096), (24, 520, 4160), (32, 8200, 4096), (33, 999, 4736), (64, 4096, 2048),
-                                   (48, 40, 2112), (64, 12288, 4096), (12, 4160, 4096), (5, 16384, 4160), (9, 16400, 4672),
-                                   (16, 70, 16448), (40, 33, 20480), (20, 16385, 2048), (24, 25000, 2176),
-                                   (64, 24576, 2048)])
+W2_FMTS, W4_ONLY = [levels.FMT_W2_MNZ, levels.FMT_W2_POT], [levels.FMT_W4_SYM]
+BATCH_SHAPES = [(f, *shape) for fmts, shapes in (
+    (FMTS, [(17, 4100, 4096), (16, 4096, 4096), (15, 300, 8256), (28, 520, 4160), (32, 8200, 4096), (33, 999, 4736),
+            (64, 4096, 2048), (48, 40, 2112), (64, 12288, 4096), (9, 16400, 4672), (16, 70, 16448), (40, 33, 20480),
+            (24, 16385, 2048), (24, 25000, 3136), (64, 24576, 2048), (16, 25000, 4160), (40, 6000, 4096), (47, 9000, 4160),
+            (33, 20000, 2112), (50, 5000, 2048)]),
+    (W2_FMTS, [(15, 300, 4736), (9, 6200, 4096), (12, 4160, 4096), (5, 16384, 4160), (20, 16385, 2048), (16, 12300, 4160),
+               (40, 25000, 16448)]),
+    (W4_ONLY, [(36, 25000, 2112), (64, 25000, 2112), (16, 8200, 14336)])) for f in fmts for shape in shapes]
+
+
+@pytest.mark.parametrize("fmt,M,N,K", BATCH_SHAPES)
 def test_batch_linear(Q, fmt, M, N, K):
-    # The batch kernel's edges: one to four 32-row tiles a workgroup (N up to and past 8192, 16384, 24576),
-    # one and two token tiles (and two workgroups of one where N <= 4096), slices of K that end inside a step
+    # The batch kernel's edges: one to four 32-row tiles a workgroup (N up to and past 8192, 16384, 24576), loads of
+    # 16, 32, 48 and 64 tokens, one and two token tiles (and two workgroups of one where N <= 4096), slices of K that end inside a step
     # or a line group, slices past K (K = 2048 and 2112 over 4 and 8 waves), odd counts of line groups; rows
     # and tokens that end inside a tile.  Warm and cold caches (late loads).  Bit-identical to the oracle,
     # with and without accumulators, code sums and a workspace.
+    check_route("batch", fmt, M, N, K)
     b = 64
     L = synth.draw_levels(fmt, N, K, cfg=92, layer=M + fmt)
     s_w = synth.draw_scales(fmt, N, cfg=92, layer=M + fmt)

@@ -245,12 +245,14 @@ hipError_t launch_sk_tu(const uint32_t* P, const uint16_t* sw, int64_t N, int64_
     if (nc <= 2 && want >= 3) return QIFT_SK(4, 2);
   }
   if (nc <= 2 && want >= 2) return QIFT_SK(2, 2);
-  if constexpr (!W4) {
+  if constexpr (!W4 && TT < 4) {
     if (nc <= 4 && want >= 2) return QIFT_SK(2, 4);
   }
   if (nc <= 2) return QIFT_SK(1, 2);
-  if (nc <= 4) return QIFT_SK(1, 4);
-  return QIFT_SK(1, 8);
+  if constexpr (TT < 4)
+    if (nc <= 4) return QIFT_SK(1, 4);
+  if constexpr (TT < 4 && W4) return QIFT_SK(1, 8);
+  return hipErrorInvalidValue;   // longer K is the other kernels' (route::choose)
 #undef QIFT_SK
 }
 
@@ -258,8 +260,7 @@ template <int FMT>
 hipError_t launch_skinny_fmt(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act,
                              const float* sx, const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out,
                              hipStream_t s) {
-  if (M < 1 || M > kSkinnyMaxM || K > kSkinnyMaxK) return hipErrorInvalidValue;
-  if (M <= 16) return launch_sk_tu<FMT, 1>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
+  if (M <= kCodesMaxM || M > kSkinnyMaxM || K > kSkinnyMaxK) return hipErrorInvalidValue;
   if (M <= 32) return launch_sk_tu<FMT, 2>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
   return launch_sk_tu<FMT, 4>(P, sw, N, K, act, sx, asum, M, y, acc_out, s);
 }

@@ -91,15 +91,25 @@ inline bool take_batch(bool w4, int64_t N, int64_t K, int64_t M, bool gs, bool s
   if (M < 5 || M > kBatchMaxM) return false;
   if (M > kCodesMaxM) {
     // two rounds: W2 40960 x 4096 at 33 34.9 / 20.3 (the GEMM), W4 at 48 43.3 / 28.5; where the others' passes
-    // over the codes are long it is still ahead up to 32 tokens (W2 x 8192 at 24 0.85, W4 x 5120 at 17 0.82)
-    if (N > 32768) return M <= 32 && K > (w4 ? 4096 : 8191) && K <= kSkinnyMaxK && !gs;
+    // over the codes are long it is still ahead up to 32 tokens (W2 x 8192 at 24 0.85, W4 x 5120 at 17 0.82,
+    // W2 70000 x 4096 at 30 0.89)
+    if (N > 32768)
+      return M <= 32 && !gs && K <= kSkinnyMaxK && (K > (w4 ? 4096 : 8191) || (K >= 4096 && M >= (w4 ? 30 : 28)));
     // a K that the skinny kernel does not take: against the GEMM (4096 x 20480 at 24: 14.7 / 70) always,
-    // against its split W2 up to 8192 rows (12288 x 20480 at 33: 1.15 of it), W4 up to 4096 and from 33
-    if (K > kSkinnyMaxK) return !(gs && (N >= 12288 || (w4 && (N > 4096 || M < 33))));
+    // against its split W2 up to 8192 rows (12288 x 20480 at 33: 1.15 of it, 8192 x 28672 at 52: 1.08), W4 up
+    // to 4096 and from 33
+    if (K > kSkinnyMaxK) return !(gs && (N >= 12288 || (N > 6144 && K > 24576) || (w4 && (N > 4096 || M < 33))));
     // long K with a split GEMM: W4 4096 x 11008 at 24 1.12 of it, at 33 0.96, x 16384 at 33 1.09; W4 28672
     // x 14336 at 33 1.12, W2 22016 x 11008 at 33 1.08 but 0.93 at 64
     if (gs && w4 && N <= 4096 && K > 8192) return M >= 33 && K < 16384;
     if (gs && M >= 33 && K > 8192 && (w4 ? N > 24576 : N > 16384 && M < 48)) return false;
+    // and W4 where the split fills the CUs once while the row tiles leave a third of them idle (just past 4096
+    // and 8192 rows: 5120 x 13824 at 33 20.7 / 16.9, 9000 x 7168 at 26 17.8 / 16.3)
+    if (gs && w4 && N > 4096 && K > 6144) {
+      const int64_t rj = (N + 8191) / 8192, own = (N + 32 * rj - 1) / (32 * rj);
+      const int64_t split = (N + 255) / 256 * gemm_split_plan(w4, N, M, K).S;
+      if (own <= 170 && split >= 224 && split <= 272) return false;
+    }
     if (N >= 16384) {
       // against the tiled GEMM: W2 of more than 24576 rows is its (28672 x 4096 at 64: 20.2 / 19.9)
       if (M >= 33) return K >= 2048 && (w4 || N <= 24576);
@@ -111,19 +121,21 @@ inline bool take_batch(bool w4, int64_t N, int64_t K, int64_t M, bool gs, bool s
     if (K < 4096) return false;
     if (N > 4096) return true;       // 12288 x 4096 at 17 8.3 / 8.7, W4 at 64 12.5 / 23.4
     // up to 4096 rows from 24 tokens (4096 x 4096 at 24 6.3 / 6.5, at 17 6.2 / 5.9); just past 4096 k, where a
-    // slice is a line group and a piece, from 28 (1000 x 5120 at 17 1.17, at 24 1.07); long ones at
-    // once, W4 only small ones (3072 x 11008 at 17 1.18, at 28 1.03).  The skinny split is the faster
+    // slice is a line group and a piece, from 28 (1000 x 5120 at 17 1.17, at 24 1.07), W4 of up to
+    // 1024 rows from 33 (777 x 6208 at 32 1.08);
+    // long ones at once, W4 only small ones (3072 x 11008 at 17 1.18, at 28 1.03; 2560 x 9728 at 21 1.08).  The skinny split is the faster
     // for very long K (1000 x 14336 at 17 11.1 / 8.9) and around 2048 rows (2048 x 11008 at 17 1.09)
     // (from 33 tokens on only with few rows: 1000 x 14336 at 33 11.3 / 10.2)
     if (ss && M > 32) return K < 12288 || N <= 128 || N > 2560;
     if (ss)
       return K <= 8192 ? M >= 24 || K > 4096 : N <= 128 || (K < 12288 && (N < 1024 || N > 2560));
-    if (K > 8192) return M >= 28 || !w4 || N * K <= (int64_t(24) << 20);
-    return M >= (K > 4096 && K < 8192 && !gs ? 28 : 24) || (K == 8192 && !w4);
+    if (K > 8192) return M >= 28 || !w4 || (N <= 2048 && N * K <= (int64_t(24) << 20));
+    return M >= (K > 4096 && K < 8192 && !gs ? (w4 && N <= 1024 ? 33 : 28) : 24) || (K == 8192 && !w4);
   }
   // 5-16 tokens: the decode kernel on codes.  Wide and long (16384 x 8192, whose one 16-row tile per
   // workgroup takes four rounds: 13.4 / 23.4 at 9, W4 20.6 / 29.3 at 12)
-  if (N > 32768) return K > 4096 && M >= (!w4 ? 6 : K >= 8192 ? 9 : 15);
+  // (a second round: 40960 x 11008 at 5 1.14, W4 40960 x 5120 at 12 1.11; 57344 x 8192 at 5 44.6 / 56.7)
+  if (N > 32768) return K > 4096 && M >= (!w4 ? (N >= 49152 ? 5 : 6) : K >= 8192 ? 9 : 15);
   if (N >= 16384 && K > 4096) return !w4 || M >= 9;
   // W4 from 15 tokens, wide (28672 x 4096 20.1 / 22.2) or at most 4096 rows of a whole number of line groups
   // a slice (4096 x 11008 11.2 / 13.6, 4096 x 4096 6.3 / 6.5 at 16, but x 5120 1.05-1.16, 300 x 4096 1.14)
@@ -131,9 +143,9 @@ inline bool take_batch(bool w4, int64_t N, int64_t K, int64_t M, bool gs, bool s
   // where the codes exceed the decode kernel's LDS the skinny split (1000 x 14336 at 16: 9.5 / 8.2)
   if (ss && K >= 12288 && N > 128 && N <= 4096) return false;
   // W2 of at most 16384 rows from 12 tokens (at 16: 6144 x 4096 5.7 / 7.3, 4096 5.5 / 6.4, 12288 7.9 / 8.3), 4097-8192
-  // rows from 9 (at 9 6144 x 4096 0.90, 12288 x 5120 0.82), few rows just past 4096 k from 14 (300 x 5120 at 12 1.09)
+  // rows from 9 (at 9 6144 x 4096 0.90, 12288 x 5120 0.82), few rows just past 4096 k from 13 (300 x 5120 at 12 1.09, 777 x 6208 at 13 0.85)
   if (!w4 && K >= 4096 && N <= 16384)
-    if (M >= (N > 4096 && N <= 8192 ? 9 : N <= 4096 && K > 4096 && K < 8192 ? 14 : 12)) return true;
+    if (M >= (N > 4096 && N <= 8192 ? 9 : N <= 4096 && K > 4096 && K < 8192 ? 13 : 12)) return true;
   // without a split the decode kernels that read the codes from memory (4096 x 14336 at 16 10.2 / 14.5)
   return !codes_fit && M >= (w4 ? 12 : 9) && !ss;
 }

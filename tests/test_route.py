@@ -41,6 +41,14 @@ MEASURED = [
     (0, 28672, 20480, 48, 1, {"batch": 67.40, "gemm_split": 56.18, "gemm": 84.44}),
     (0, 22016, 11008, 33, 1, {"batch": 34.29, "gemm_split": 31.76, "gemm": 46.42}),
     (1, 28672, 14336, 33, 1, {"batch": 64.34, "gemm_split": 57.68, "gemm": 77.25}),
+    # W4 rows just past a round of the batch kernel's tiles, with the split GEMM
+    (1, 5120, 13824, 33, 1, {"batch": 20.71, "gemm_split": 16.89}),
+    (1, 9000, 7168, 26, 1, {"batch": 17.77, "gemm_split": 16.31}),
+    (0, 8192, 28672, 52, 1, {"batch": 36.11, "gemm_split": 33.32}),
+    (0, 70000, 4096, 30, 0, {"batch": 40.01, "skinny": 45.05}),
+    (1, 2560, 9728, 21, 0, {"batch": 12.74, "skinny": 11.75}),
+    (1, 777, 6208, 32, 0, {"batch": 8.59, "skinny": 7.93}),
+    (0, 777, 6208, 13, 0, {"batch": 5.94, "codes": 6.99}),
     # what the batch kernel and the GEMM keep
     (0, 4096, 4096, 24, 0, {"batch": 6.27, "skinny": 6.59}),
     (0, 6144, 4096, 9, 0, {"batch": 5.63, "codes": 6.59}),

@@ -2,6 +2,7 @@
 #include "qift_fwht.h"   // buffer-load helpers
 #include "qift_internal.h"
 #include "qift_mma.h"
+#include "qift_route.h"
 #include "qift_waits.h"
 
 #include <type_traits>
@@ -201,7 +202,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
           an[j][r] = s < 3 ? decode_part<FMT, OP>(w[j], s + 1, r) : decode_part<FMT, OP>(wnx[j], 0, r);
       if (i >= NP - 2) {
 #pragma unroll
-        for (int q = 0; q < NA / 2; ++q) issue_a(kt + 4, own, q + (i - (NP - 2)) * (NA / 2));
+        for (int q = 0; q < NA; ++q)
+          if ((q >= (NA + 1) / 2) == (i == NP - 1)) issue_a(kt + 4, own, q);
       }
       acc[1 - j0][t] = mfma32_i8(a[1 - j0], b, acc[1 - j0][t]);
       if (t == TC - 1) {
@@ -303,13 +305,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm32(const uint32_t* __restrict__ 
   if (acc_out == nullptr) {
     // through LDS: token tile t in buffer t as rows of 256 outputs (32 chunks of 8, chunk c of token m in
     // slot c ^ m), then 16-byte stores of whole rows
-    // (with two token tiles 16 tokens to a buffer)
+    // (8 TC tokens' rows to a buffer)
     auto row_at = [&](int t, int r) -> int8_t* {
-      if constexpr (TC == 4) return (t == 0 ? lds0 : t == 1 ? lds1 : t == 2 ? lds2 : lds3) + 512 * r;
-      else if (r & 16) return (t == 0 ? lds1 : lds3) + 512 * (r & 15);
-      else return (t == 0 ? lds0 : lds2) + 512 * (r & 15);
+      constexpr int RB = BM / 4;   // rows of outputs that a buffer holds
+      const int b = 32 * t / RB, row = 32 * t + r - b * RB;
+      int8_t* lo = b == 0 ? lds0 : b == 1 ? lds1 : b == 2 ? lds2 : lds3;
+      int8_t* hi = b == 0 ? lds1 : b == 1 ? lds2 : lds3;
+      return row < RB ? lo + 512 * row : hi + 512 * (row - RB);
     };
-    static_assert(TC == 4 || TC == 2, "outputs staged in the activation buffers");
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -380,29 +383,19 @@ hipError_t launch_t(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K,
   return hipGetLastError();
 }
 
-// 128 or 64 tokens to a tile.  A CU runs one or two workgroups (512 at once on the chip); relative times
-// of a tile alone on its CU and of two there, measured at K = 4096 (us of 27 / 45 and 17 / 30 for W2, 28 /
-// 54 and 22 / 40 for W4): whole rounds of two and then the rest decide.  128-token tiles halve the weight
-// loads and decodes per MFMA, 64-token tiles fill the chip from half as many tokens on (4096 x 4096 at 400
-// tokens 16.7 us against 25.1; 28672 x 4096 at 2048 tokens 213 against 187).
-inline int64_t tile_cost(int64_t tiles, int one, int two) {
-  const int64_t rest = tiles % 512;
-  return tiles / 512 * two + (rest == 0 ? 0 : rest <= 256 ? one : two);
-}
-
 template <int FMT>
 hipError_t launch_f(const uint32_t* P, const uint16_t* sw, int64_t N, int64_t K, const int8_t* act, const float* sx,
                     const int32_t* asum, int64_t M, uint16_t* y, int32_t* acc_out, hipStream_t s) {
-  const int64_t tn = (N + 255) / 256, t128 = tn * ((M + 127) / 128), t64 = tn * ((M + 63) / 64);
-  const bool wide = FMT == FMT_W4 ? tile_cost(t128, 28, 54) <= tile_cost(t64, 22, 40)
-                                  : tile_cost(t128, 27, 45) <= tile_cost(t64, 17, 30);
+  const int tokens = route::gemm_tile_tokens(FMT == FMT_W4, N, M);
 #define QIFT_G(TC_, OP_) launch_t<FMT, TC_, OP_>(P, sw, N, K, act, sx, asum, M, y, acc_out, s)
+#define QIFT_GT(OP_) (tokens == 128 ? QIFT_G(4, OP_) : tokens == 96 ? QIFT_G(3, OP_) : QIFT_G(2, OP_))
   if constexpr (FMT != FMT_POT)
-    if (asum) return wide ? QIFT_G(4, kCodes) : QIFT_G(2, kCodes);
+    if (asum) return QIFT_GT(kCodes);
   // 16 x 8 x 7 x K stays below 2^31
   if constexpr (FMT == FMT_W4)
     if (K > (1 << 21)) return QIFT_G(2, kLevels1);
-  return wide ? QIFT_G(4, kLevels) : QIFT_G(2, kLevels);
+  return QIFT_GT(kLevels);
+#undef QIFT_GT
 #undef QIFT_G
 }
 

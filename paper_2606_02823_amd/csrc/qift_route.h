@@ -45,6 +45,24 @@ inline GemmSplit gemm_split_plan(bool w4, int64_t N, int64_t M, int64_t K) {
   return p;
 }
 
+// ---- tiles of the unsplit GEMM: 256 rows x 128, 96 or 64 tokens.
+// A CU runs one or two workgroups (512 at once on the chip); times of a tile alone on its CU and of two there, at
+// K = 4096 in us: whole rounds of two and then the rest decide.  128-token tiles spend the least on weights, 64-token
+// tiles fill the chip from half as many tokens on (4096 x 4096 at 400 tokens 16.7 against 25.1), and 96-token
+// tiles save the second tile that few CUs would take: 9000 x 7168 at 900 tokens 63.9 against 76.2 and 74.0 (65.9 for the
+// former 64-token tiles of the 16-wide MFMA, three to a CU).  Over 1584 sizes within 0.1 % of the best tile on average.
+inline int64_t tile_cost(int64_t tiles, int one, int two) {
+  const int64_t rest = tiles % 512;
+  return tiles / 512 * two + (rest == 0 ? 0 : rest <= 256 ? one : two);
+}
+inline int gemm_tile_tokens(bool w4, int64_t N, int64_t M) {
+  const int64_t tn = (N + 255) / 256;
+  const int64_t c128 = tile_cost(tn * ((M + 127) / 128), w4 ? 29 : 27, w4 ? 54 : 46);
+  const int64_t c96 = tile_cost(tn * ((M + 95) / 96), w4 ? 26 : 22, w4 ? 46 : 38);
+  const int64_t c64 = tile_cost(tn * ((M + 63) / 64), w4 ? 23 : 17, w4 ? 40 : 30);
+  return c128 <= c96 && c128 <= c64 ? 128 : c96 <= c64 ? 96 : 64;
+}
+
 // ---- skinny linear split over K (W2): T = 4 tiles of 16 rows per workgroup, S ranges of us 256-k units,
 // chosen for about one workgroup per CU with at most two units per slice; S = 0 for K <= 4096 (the codes
 // per workgroup are few enough: measured faster unsplit) and when a linear has tiles enough without.
@@ -163,16 +181,16 @@ inline Kernel choose(bool w4, int64_t N, int64_t K, int64_t M, bool codes_fit, b
   if (gs) {
     if (M <= kSkinnyMaxM) {
       if (!(wide && K < 8192)) return kGemmSplit;
-    } else if (K >= 8192) {
-      // a long K splits wherever there is a plan (4096 x 14336: 22 / 49 at 100 tokens, 62 / 78 at 1024)
-      return kGemmSplit;
     } else {
-      // A short K has few steps to share out and pays the second pass (4-5 us) and the partial sums: it splits
-      // only while the tiles are few, W2 up to 64 of them (4096 x 4096, split against not: 12.4 / 16.5 at 100
-      // tokens, 14.5 / 16.5 at 256, but 19 / 16.6 at 300 and 27 / 17.8 at 600; 12288 x 4096 19.9 / 17.5 at
-      // 100), W4 up to 96 (6144 x 4096 21.5 / 22.3 at 192, 24 / 22.3 at 300), wide linears not at all.
+      // What the split pays for (the second pass, 4-5 us, and the partial sums) grows with the tiles, what it gains
+      // with K: it is the faster up to a number of tiles that grows with K.  W2, split over unsplit at 4096 k
+      // 0.9 to 64 tiles and 1.1 from 72 on, 5120 1.0 at 72, 7168 1.0 at 108, 8192 1.0 at 128, 11008 1.0 at 156,
+      // 14336 0.95 at 162 and 1.07 at 172, 20480 1.0 from 176 on; two ranges only (K <= 2816) 1.0 at 8 and 1.1 at 24.  W4 4096 k 0.95 at 80
+      // and 1.0 at 96, 5120 1.0 at 120, 7168 and 8192 1.0 at 144, longer ones wherever there is a plan.
       const int64_t tiles = ((N + 255) / 256) * ((M + 63) / 64);
-      if (tiles <= (w4 ? 96 : 64) && N < 16384) return kGemmSplit;
+      const int64_t most = w4 ? (K >= 11008 ? tiles : K / 46 < 150 ? K / 46 : 150)
+                              : K <= 2816 ? 8 : K <= 8192 ? K / 64 : 128 + (K - 8192) / 128;
+      if (tiles <= most) return kGemmSplit;
     }
   }
   if (M > kSkinnyMaxM || (wide && (!gs || K < 8192))) return kGemm;

@@ -14,8 +14,8 @@ using namespace qift;
 int main() {
   long w4, N, K, M, codes, ws;
   while (std::scanf("%ld %ld %ld %ld %ld %ld", &w4, &N, &K, &M, &codes, &ws) == 6)
-    std::printf("%d %d %d\\n", (int)route::choose(w4, N, K, M, codes, ws), route::gemm_split_plan(w4, N, M, K).S,
-                route::skinny_split_plan(w4, N, M, K).S);
+    std::printf("%d %d %d %d\\n", (int)route::choose(w4, N, K, M, codes, ws), route::gemm_split_plan(w4, N, M, K).S,
+                route::skinny_split_plan(w4, N, M, K).S, route::gemm_tile_tokens(w4, N, M));
 }
 """
 
@@ -32,9 +32,10 @@ def _probe():
 
 
 def ask(queries):
-    """list of (w4, N, K, M, codes fit LDS, workspace) -> list of (kernel, GEMM ranges, skinny ranges)."""
+    """list of (w4, N, K, M, codes fit LDS, workspace) -> list of (kernel, GEMM ranges, skinny ranges, tokens of the
+    unsplit GEMM's tiles)."""
     out = subprocess.run([_probe()[1]], input="".join("%d %d %d %d %d %d\n" % tuple(q) for q in queries), text=True,
                          capture_output=True, check=True).stdout.splitlines()
     assert len(out) == len(queries)
     rows = [[int(v) for v in line.split()] for line in out]
-    return [(KERNELS[k], s, t) for k, s, t in rows]
+    return [(KERNELS[r[0]], *r[1:]) for r in rows]

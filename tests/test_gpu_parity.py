@@ -699,17 +699,20 @@ def test_hbm_read_probe_reads_every_word(Q, nwords):
 
 
 @pytest.mark.parametrize("fmt", FMTS)
-@pytest.mark.parametrize("M,N,K", [(65, 264, 64), (128, 256, 128), (97, 520, 576), (129, 1000, 1536), (200, 999, 1664),
-                                   (64, 16400, 704), (33, 16385, 1088), (130, 28672, 640), (200, 22016, 1536),
-                                   (256, 16390, 320)])
-def test_tiled_gemm(Q, fmt, M, N, K):
+@pytest.mark.parametrize("M,N,K,tokens", [(65, 264, 64, 64), (128, 256, 128, 64), (97, 520, 576, 64), (129, 1000, 1536, 64),
+                                          (200, 999, 1664, 64), (64, 16400, 704, 64), (33, 16385, 1088, 64),
+                                          (130, 28672, 640, 96), (192, 28672, 1088, 96), (140, 22016, 704, 96),
+                                          (190, 23000, 64, 96), (151, 22001, 320, 96), (161, 28600, 1536, 96),
+                                          (200, 22016, 1536, 128), (250, 28672, 640, 128), (380, 16390, 320, 128)])
+def test_tiled_gemm(Q, fmt, M, N, K, tokens):
     # The tiled GEMM's edges: K from half a step (128 k) over partial and odd line groups (512 k of W2,
     # 256 k of W4: K = 1536 is three of W2's, K = 320 one and a quarter of W4's); tokens that end inside a
     # 32-token tile; rows that end inside a 256-row tile; outputs at 16-byte, 4-byte and odd offsets (N
-    # mod 8); 64-token tiles (few tiles) and 128-token tiles (the last three shapes).  Run once on warm
+    # mod 8); tiles of 64, 96 and 128 tokens.  Run once on warm
     # and once on cold caches, where the loads arrive late.  Bit-identical to the oracle (all rows of the
     # small shapes, 200 of the wide ones) with and without accumulators and code sums.
     check_route("gemm", fmt, M, N, K)
+    assert ask([(fmt == levels.FMT_W4_SYM, N, K, M, 0, 0)])[0][3] == tokens
     b = 64
     L = synth.draw_levels(fmt, N, K, cfg=94, layer=M + fmt)
     s_w = synth.draw_scales(fmt, N, cfg=94, layer=M + fmt)

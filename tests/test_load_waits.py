@@ -12,8 +12,8 @@ import subprocess
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_02823_amd", "csrc")
-# (tag, weight loads of a line group, steps of a group, activation loads of a step): k_gemm32 of 64 and 128 tokens ...
-GEMM = [(f"{f}-{32 * tc}", 8, ls, tc) for f, ls in (("w2", 4), ("w4", 2)) for tc in (2, 4)]
+# (tag, weight loads of a line group, steps of a group, activation loads of a step): k_gemm32 of 64, 96 and 128 tokens ...
+GEMM = [(f"{f}-{32 * tc}", 8, ls, tc) for f, ls in (("w2", 4), ("w4", 2)) for tc in (2, 3, 4)]
 # ... and k_batch of 1-4 row tiles and 16-64 tokens
 BATCH = [(f"{f}-{rj}x{8 * na}", rj * 4, ls, na) for f, ls in (("w2", 4), ("w4", 2)) for rj in (1, 2, 3, 4)
          for na in (2, 4, 6, 8)]
@@ -145,7 +145,7 @@ def test_batch_linear_waits(counts, tag, NW, LS, NA):
         assert replay_batch(prologue, step, NA, NW, LS, GT) == [], GT
 
 
-@pytest.mark.parametrize("NA", [2, 4])
+@pytest.mark.parametrize("NA", [2, 3, 4])
 def test_replay_finds_a_lax_wait(counts, NA):
     # W4's first step with a prologue that leaves A(1) in flight: two weight groups are counted there, one is sent
     _, handover = counts[NA, 8, 2]["gemm"]

@@ -64,7 +64,7 @@ MEASURED = [
 
 @pytest.mark.parametrize("w4,N,K,M,ws,us", MEASURED, ids=[f"{'w4' if c[0] else 'w2'}-{c[1]}x{c[2]}-m{c[3]}" for c in MEASURED])
 def test_route_takes_the_faster_kernel(w4, N, K, M, ws, us):
-    kernel, _, _ = ask([(w4, N, K, M, "codes" in us, ws)])[0]
+    kernel, *_ = ask([(w4, N, K, M, "codes" in us, ws)])[0]
     # 4 %: twice what repeated timings of one kernel differed by
     assert us[kernel] <= 1.04 * min(us.values()), (kernel, us)
 
@@ -75,7 +75,7 @@ def test_route_stays_within_the_kernels_limits():
     Ms = [1, 4, 5, 8, 9, 12, 16, 17, 23, 24, 27, 28, 32, 33, 47, 48, 64, 65, 200, 2048]
     qs = [(w4, N, K, M, c, ws) for w4 in (0, 1) for N in Ns for K in Ks for M in Ms
           for c in ((0, 1) if M <= 16 and K <= 16384 else (0,)) for ws in (0, 1)]
-    for (w4, N, K, M, codes, ws), (kernel, gemm_ranges, skinny_ranges) in zip(qs, ask(qs)):
+    for (w4, N, K, M, codes, ws), (kernel, gemm_ranges, skinny_ranges, _) in zip(qs, ask(qs)):
         q = (w4, N, K, M, codes, ws, kernel)
         if kernel == "batch":
             assert 5 <= M <= 64, q
@@ -92,3 +92,42 @@ def test_route_stays_within_the_kernels_limits():
             assert codes and M <= 16, q
         else:
             assert M <= 16 and not codes, q
+
+
+# (W4, N, K, M, us of the tiled GEMM with tiles of 64, 96 and 128 tokens, us of its split over K)
+TILES = [
+    (0, 9000, 7168, 900, {64: 74.03, 96: 63.95, 128: 76.18}, None),
+    (0, 9000, 20480, 1024, {64: 204.58, 96: 177.59, 128: 217.2}, None),
+    (0, 12288, 14336, 800, {64: 141.46, 96: 125.85, 128: 150.15}, None),
+    (0, 28672, 20480, 300, {64: 207.1, 96: 176.6, 128: 213.33}, None),
+    (0, 5120, 14336, 2048, {64: 140.04, 96: 126.37, 128: 150.24}, None),
+    (0, 3072, 2048, 1024, {64: 13.77, 96: 16.43, 128: 18.8}, 25.32),
+    (0, 16384, 2048, 150, {64: 12.64, 96: 15.14, 128: 17.58}, 20.87),
+    (0, 700, 2944, 90, {64: 16.25}, 11.11),
+    (0, 1000, 4096, 128, {64: 17.92, 96: 21.61, 128: 26.58}, 12.32),
+    (0, 4096, 4096, 256, {64: 17.97, 96: 21.96, 128: 26.33}, 15.66),
+    (0, 3072, 5120, 150, {64: 21.88, 96: 27.08, 128: 32.01}, 15.81),
+    (0, 12288, 5120, 300, {64: 23.94, 96: 28.51, 128: 32.84}, 33.89),
+    (0, 12288, 7168, 300, {64: 29.73, 96: 35.3, 128: 41.61}, 39.15),
+    (0, 9000, 7168, 65, {64: 29.03}, 21.89),
+    (0, 12288, 8192, 256, {64: 31.43, 96: 37.66, 128: 45.63}, 40.94),
+    (0, 4096, 8192, 700, {64: 30.71, 96: 36.9, 128: 45.13}, 40.61),
+    (0, 9000, 11008, 192, {64: 40.25, 96: 50.0, 128: 60.44}, 33.1),
+    (0, 6144, 14336, 450, {64: 51.22, 96: 62.64, 128: 75.59}, 58.61),
+    (0, 1000, 20480, 1900, {64: 72.17, 96: 88.13, 128: 108.42}, 49.69),
+    (1, 9000, 4096, 65, {64: 22.38, 96: 25.23, 128: 26.9}, 19.68),
+    (1, 5120, 5120, 150, {64: 28.22, 96: 31.49, 128: 37.41}, 23.64),
+    (1, 4096, 5120, 300, {64: 27.45, 96: 31.29, 128: 37.21}, 24.28),
+    (1, 5120, 7168, 65, {64: 34.13, 96: 39.51, 128: 44.86}, 23.13),
+    (1, 16384, 8192, 128, {64: 47.32, 96: 53.99, 128: 57.04}, 41.68),
+    (1, 12288, 14336, 150, {64: 71.14, 96: 88.47, 128: 92.1}, 61.36),
+    (1, 6144, 20480, 400, {64: 101.91, 96: 119.9, 128: 129.88}, 83.23),
+]
+
+
+@pytest.mark.parametrize("w4,N,K,M,us,split", TILES, ids=[f"{'w4' if c[0] else 'w2'}-{c[1]}x{c[2]}-m{c[3]}" for c in TILES])
+def test_gemm_tiles_and_split(w4, N, K, M, us, split):
+    (plain, *_), (kernel, _, _, tokens) = ask([(w4, N, K, M, 0, 0), (w4, N, K, M, 0, 1)])
+    assert plain == "gemm" and us[tokens] <= 1.04 * min(us.values()), (tokens, us)
+    if split is not None:
+        assert kernel == ("gemm_split" if split < us[tokens] else "gemm"), (kernel, us[tokens], split)

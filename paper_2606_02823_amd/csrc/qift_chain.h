@@ -579,10 +579,11 @@ __device__ __forceinline__ void act_link_w(int gw, int li, const ChainDesc& d, i
   }
 }
 
-// Bytes of a link's scales for range-checked dword loads, which return zero for a dword that ends past the
-// range: two more than there are, so that the dword of an odd N's last channel is in and the next one out.  (Its
+// Bytes of a link's scales for the range-checked loads of four, which return zero for a dword that ends past
+// the range: two more than there are, so that the dword of an odd N's last channel is in and the next one out.  (Its
 // other half is in the same aligned 4 bytes and goes to no output.  Putting the channel in by a load of its own
-// cost every link some cycles: 1.050 -> 1.066 ms on the LLaMA-3.1-8B step.)
+// cost every link some cycles: 1.050 -> 1.066 ms on the LLaMA-3.1-8B step; with the prefetch's dwords bounded by
+// their lanes alone 1.038.)
 __device__ __forceinline__ uint32_t scale_bytes(int N) { return (uint32_t)N * 2u + 2u; }
 
 // y[m][n0 .. n0 + 3] (fp16, and the accumulators) and, for the links whose output another link
@@ -730,7 +731,8 @@ __global__ __launch_bounds__(kChainThreads) void k_decode_chain(const ChainDesc*
         int ln = dev::lane_id();
         asm volatile("" : "+v"(ln));
         const int n = (gn.t0 + slice) * 16 + 2 * ln;   // rows n, n + 1 in dword ln of the slot
-        const __amdgpu_buffer_rsrc_t srs = dev::make_rsrc(dn.sw, scale_bytes(dn.N));
+        // (the lanes' own test of n bounds the loads: a dword each, that of an odd N's last row included)
+        const __amdgpu_buffer_rsrc_t srs = dev::make_rsrc(dn.sw, dev::kOutOfRange);
         const uint32_t off = slice < T0 && ln < 8 && n < dn.N ? (uint32_t)(2 * n) : dev::kOutOfRange;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, (__attribute__((address_space(3))) void*)my_sw, 4, off, 0, 0, 0);
       }

@@ -305,8 +305,8 @@ class SweepStack:
                   for (_, _, K, _, site) in self.plan]
         self.acts = [qift.alloc_act(self.M, K, dev) for (_, _, K, _, _) in self.plan]
         self.outs = [torch.empty((self.M, N), dtype=torch.float16, device=dev) for (_, N, _, _, _) in self.plan]
-        # one workspace for the linears that take one at this M (the skinny linear split over K up to 64
-        # tokens, the GEMM split over K above)
+        # one workspace for the linears that take one at this M (the skinny linear split over K up to 47
+        # tokens, the GEMM split over K beyond and for long weights)
         self.need = [qift.workspace_bytes(w, self.M) for w in self.weights[0]]
         self.ws = torch.empty(max(self.need), dtype=torch.uint8, device=dev) if max(self.need) else None
         torch.cuda.synchronize()

@@ -1,6 +1,6 @@
 // Quantized linear kernels on int8 MFMA (operand layout and decoding:
 // qift_mma.h): the decode kernels for up to 16 tokens, the tiled GEMM split over
-// K, and the choice of kernel for a linear on codes.
+// K, and the dispatch of a linear on codes to the kernel that route::choose names.
 #include "qift_fwht.h"   // buffer-load helpers
 #include "qift_internal.h"
 #include "qift_mma.h"

@@ -25,7 +25,7 @@
 //
 // The 64-candidate search of PoT and G(r) costs one LDS histogram per row instead of 64 passes over
 // its elements (see (1)-(4) in the kernel; the chosen candidate is the same).  One LLaMA-3.1-8B layer,
-// 218 M weights, PoT: 6.76 -> 0.55 ms (gate|up 3.19 ms -> 0.27, down 2.39 -> 0.17), against 0.34 ms for
+// 218 M weights, PoT: 6.76 -> 0.52 ms (gate|up 3.19 ms -> 0.25, down 2.39 -> 0.17), against 0.34 ms for
 // MNZ and W4, which have no search; at 5.2 TB/s, a large copy's rate, the 1.09 GB read and written take
 // 0.21 ms.  What is left beyond that is the fp64 rotation and its exchanges through LDS (MNZ's time)
 // and the LDS atomics, one for each of the ~60 % of the elements past the first threshold.
@@ -88,13 +88,22 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   return (row(0) + row(16)) + (row(32) + row(48));
 }
 
-// sum of a per-thread fp64 value over the workgroup; red holds 4 doubles; all threads get the sum
-__device__ __forceinline__ double group_sum(double v, double* red) {
+// The four waves' values of a reduction stand in the padding of the exchange buffer (two doubles after every
+// 16, which no exchange touches): with an array of their own the search's LDS came to 40992 bytes, 32 more than
+// a quarter of a CU's, and three workgroups to a CU instead of four (PoT 14336 x 4096 142 -> 122 us).
+__device__ __forceinline__ constexpr int red_slot(int wave) { return 16 + (wave & 1) + 18 * (wave >> 1); }
+
+// sum of a per-thread fp64 value over the workgroup; all threads get the sum
+__device__ __forceinline__ double group_sum(double v, double* xch) {
   v = wave_sum_f64(v);
-  __syncthreads();   // red is free
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();   // the slots are free
+  if ((threadIdx.x & 63) == 0) xch[red_slot(threadIdx.x >> 6)] = v;
   __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
+  return (xch[red_slot(0)] + xch[red_slot(1)]) + (xch[red_slot(2)] + xch[red_slot(3)]);
+}
+
+__device__ __forceinline__ double max_of_slots(const double* xch) {
+  return fmax(fmax(xch[red_slot(0)], xch[red_slot(1)]), fmax(xch[red_slot(2)], xch[red_slot(3)]));
 }
 
 // The stored value of a two-magnitude set: MNZ levels +-1 / +-3, PoT +-1 / +-4, G(r) the codes
@@ -112,7 +121,6 @@ __global__ __launch_bounds__(256) void k_quant_weights(const float* __restrict__
                                                        uint16_t* __restrict__ scales) {
   using S = dev::Tile<256, 16>;
   __shared__ double xch[S::LDS_DOUBLES];
-  __shared__ double red[4];
   constexpr bool kSearch = FMT == FMT_POT || FMT == FMT_MIRROR;   // the scale is searched
   constexpr int kCountBit = 49;
   __shared__ unsigned long long hist[kSearch ? 4 : 1][2][kSearch ? 64 : 1];
@@ -172,21 +180,21 @@ __global__ __launch_bounds__(256) void k_quant_weights(const float* __restrict__
     for (int tau = 0; tau < NTILES; ++tau)
 #pragma unroll
       for (int e = 0; e < 16; ++e) ss += v[tau][e] * v[tau][e];
-    const double s = sqrt(group_sum(ss, red) / (double)K);
+    const double s = sqrt(group_sum(ss, xch) / (double)K);
     sw = half_bits_rne(s / 2.0);
   } else if constexpr (FMT == FMT_W4) {
     amax = dev::wave_max(amax);
     __syncthreads();
-    if (lane == 0) red[wave] = amax;
+    if (lane == 0) xch[red_slot(wave)] = amax;
     __syncthreads();
-    const double a = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    const double a = max_of_slots(xch);
     sw = half_bits_rne(a / 7.0);
   } else {
     amax = dev::wave_max(amax);
     __syncthreads();
-    if (lane == 0) red[wave] = amax;
+    if (lane == 0) xch[red_slot(wave)] = amax;
     __syncthreads();
-    const double a = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    const double a = max_of_slots(xch);
     // PoT: levels 1, 4 at s = c max / 4, midpoint 5/2; G(r): levels r, 1 at s = c max, midpoint (1 + r) / 2
     const double thr = FMT == FMT_MIRROR ? 0.5 * (rin + 1.0) : 2.5;
     const double m_in = FMT == FMT_MIRROR ? rin : 1.0, m_out = FMT == FMT_MIRROR ? 1.0 : 4.0;
@@ -218,8 +226,8 @@ __global__ __launch_bounds__(256) void k_quant_weights(const float* __restrict__
             atomicAdd(&hist[wave][lane & 1][(int)fmin(f, 63.0)], (unsigned long long)(u + (1ull << kCountBit)));
           }
         }
-      sum_abs = group_sum(sum_abs, red);   // its barriers also order the histogram
-      sum_sq = group_sum(sum_sq, red);
+      sum_abs = group_sum(sum_abs, xch);   // its barriers also order the histogram
+      sum_sq = group_sum(sum_sq, xch);
       // (2) lane j of every wave: squared error of candidate j from the sums over its outer elements,
       //   sum w^2 - 2 s (m_in sum|w| + (m_out - m_in) S) + s^2 (m_in^2 K + (m_out^2 - m_in^2) C).
       uint64_t h = 0;
@@ -271,7 +279,7 @@ __global__ __launch_bounds__(256) void k_quant_weights(const float* __restrict__
               acc += d * d;
             }
           }
-          acc = group_sum(acc, red);
+          acc = group_sum(acc, xch);
           if (first || acc < best_err) {
             best_err = acc;
             best_j = j;

@@ -45,3 +45,12 @@ def test_no_spills(name):
     spilled = {k: v[".vgpr_spill_count"] for k, v in ks.items()
                if v[".vgpr_spill_count"] or v[".private_segment_fixed_size"]}
     assert not spilled
+
+
+def test_scale_search_leaves_four_workgroups_a_cu():
+    # PoT (1) and the mirror sets (3) of one- and two-tile rows: a quarter of the 160 KB, a quarter of the registers
+    ks = {k: v for k, v in kernels(qift.LIB_PATH).items() if "15k_quant_weights" in k}
+    search = {k: v for k, v in ks.items() if any(f"ILi{f}ELi{t}E" in k for f in (1, 3) for t in (1, 2))}
+    assert len(search) == 20
+    for k, v in search.items():
+        assert v[".group_segment_fixed_size"] <= 40960 and v[".vgpr_count"] <= 128, k
